@@ -398,6 +398,8 @@ void ssm_release_cache(void);
  *   per-pivot launches, cooperative grid over padded rows),
  *   select_hyb 1 (in mode 4: each pruned BFS by one block of the grid,
  *   the argmax by all of it),
+ *   select_ahead -1|N (no searches ahead of their turn, or N workgroups of
+ *   them whatever the graph's size, as far as its visited bits fit in LDS),
  *   select_blocks N, select_threads 256|512, select_ell 2 (plain CSR),
  *   select_m8 2 (no LDS byte copy), select_rowq 2, select_pre 1|3,
  *   select_wave -1|2 (block levels only, two passes per wave level),

@@ -670,10 +670,21 @@ __device__ __forceinline__ void claim(const int (&u)[N], bool (&ok)[N], unsigned
     for (int j = 0; j < N; ++j) ok[j] = ok[j] && !(old[j] & (1u << (u[j] & 31)));
 }
 
+// Entries of the current frontier held in LDS.
+__device__ __forceinline__ int split(const Frontier&) { return kLdsQ; }
+
+// Node u into slot `slot` of the next frontier.
+__device__ __forceinline__ void put(const Frontier& f, int slot, int u) {
+    if (slot < kLdsQ)
+        f.lnxt[slot] = u;
+    else
+        f.gnxt[slot - kLdsQ] = u;
+}
+
 // Appends the u[j] with ok[j] to the next frontier: one reservation per wave.
 // Call with every lane of the wave active.
-template <int N>
-__device__ __forceinline__ void append(const int (&u)[N], const bool (&ok)[N], const Frontier& f) {
+template <int N, class F>
+__device__ __forceinline__ void append(const int (&u)[N], const bool (&ok)[N], const F& f) {
     uint64_t mk[N];
     int tot = 0;
 #pragma unroll
@@ -687,13 +698,7 @@ __device__ __forceinline__ void append(const int (&u)[N], const bool (&ok)[N], c
     at = __builtin_amdgcn_readfirstlane(at);  // lane 0 is active: every lane is
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        if (ok[j]) {
-            const int slot = at + mask_rank(mk[j]);
-            if (slot < kLdsQ)
-                f.lnxt[slot] = u[j];
-            else
-                f.gnxt[slot - kLdsQ] = u[j];
-        }
+        if (ok[j]) put(f, at + mask_rank(mk[j]), u[j]);
         at += __popcll(mk[j]);
     }
 }
@@ -704,8 +709,8 @@ __device__ __forceinline__ void append(const int (&u)[N], const bool (&ok)[N], c
 // padding) and sets ok[j] for those that join the next frontier.  Ends with
 // every thread past a barrier and the next frontier complete; returns its
 // size.  Call from uniform control flow with blockDim.x a multiple of 64.
-template <int W, int P, bool GLOBAL_PART, typename Take>
-__device__ __forceinline__ void ell_passes(int n, const int* __restrict__ ell, int qbeg, int qend, const Frontier& f,
+template <int W, int P, bool GLOBAL_PART, class F, typename Take>
+__device__ __forceinline__ void ell_passes(int n, const int* __restrict__ ell, int qbeg, int qend, const F& f,
                                            Take& take) {
     constexpr int VW = W / 4;
     const int sub = threadIdx.x % VW, grp = threadIdx.x / VW, ngrp = blockDim.x / VW;
@@ -722,7 +727,7 @@ __device__ __forceinline__ void ell_passes(int n, const int* __restrict__ ell, i
             // LDS load would make every LDS read wait for all outstanding
             // global stores
             if (GLOBAL_PART)
-                v[p] = qi < qend ? ((const __attribute__((address_space(1))) int*)f.gcur)[qi - kLdsQ] : -1;
+                v[p] = qi < qend ? ((const __attribute__((address_space(1))) int*)f.gcur)[qi - split(f)] : -1;
             else
                 v[p] = qi < qend ? ((const __attribute__((address_space(3))) int*)f.lcur)[qi] : -1;
             nb[p] = make_int4(-1, -1, -1, -1);
@@ -755,12 +760,13 @@ __device__ __forceinline__ void ell_passes(int n, const int* __restrict__ ell, i
 // padding) and sets ok[j] for those that join the next frontier.  Ends with
 // every thread past a barrier and the next frontier complete; returns its
 // size.  Call from uniform control flow with blockDim.x a multiple of 64.
-template <int W, int P, typename Take>
+template <int W, int P, class F, typename Take>
 __device__ __forceinline__ int ell_level(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                                         const int* __restrict__ ell, int len, const Frontier& f, Take take) {
+                                         const int* __restrict__ ell, int len, const F& f, Take take) {
     static_assert(W / 4 >= 1 && W / 4 <= kWave && (kWave % (W / 4)) == 0, "lanes per node");
-    ell_passes<W, P, false>(n, ell, 0, min(len, kLdsQ), f, take);
-    if (len > kLdsQ) ell_passes<W, P, true>(n, ell, kLdsQ, len, f, take);  // uniform
+    const int lds = split(f);
+    ell_passes<W, P, false>(n, ell, 0, min(len, lds), f, take);
+    if (len > lds) ell_passes<W, P, true>(n, ell, lds, len, f, take);  // uniform
     __syncthreads();
     const int2 c = *f.cnt;  // long rows, next frontier so far
     const int nh = min(c.x, n);
@@ -789,9 +795,9 @@ __device__ __forceinline__ int ell_level(int n, const int* __restrict__ rp, cons
 
 // ell_level with P = 4 rows per lane group and pass for frontiers wider than
 // one pass, P = 1 otherwise (uniform choice).
-template <int W, typename Take>
+template <int W, class F, typename Take>
 __device__ __forceinline__ int ell_level_auto(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                                              const int* __restrict__ ell, int len, const Frontier& f, Take take) {
+                                              const int* __restrict__ ell, int len, const F& f, Take take) {
     if (len > (int)blockDim.x / (W / 4)) return ell_level<W, 4>(n, rp, ci, ell, len, f, take);
     return ell_level<W, 1>(n, rp, ci, ell, len, f, take);
 }
@@ -2173,12 +2179,13 @@ __device__ __forceinline__ int wave_levels(int n, const int* __restrict__ rp, co
 //       the byte, at or above it global m decides.  The argmax scans the
 //       bytes (and clears the flags) unless the maximum is saturated.
 //   otherwise: LDS visited bits, global m.
+// t0 = 1: pivots 0 and 1 are known and m holds pivot 0's distances.
 // The claiming lane owns m[v] for the level and writes it with plain
 // stores.  gq holds 3 n ints.
 template <int W, bool M8, int SPOOL = kSelPool>
 __device__ __forceinline__ void select_ell_body(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                 const int* __restrict__ ell, int k, int first, int* pivots, int* m,
-                                                int* gq, int* status, int wave_mode = 1) {
+                                                int* gq, int* status, int wave_mode = 1, int t0 = 0) {
     __shared__ __align__(16) unsigned char pool[SPOOL];
     __shared__ int2 s_slot[3];
     __shared__ int s_src;
@@ -2195,10 +2202,11 @@ __device__ __forceinline__ void select_ell_body(int n, const int* __restrict__ r
     int* gh = gb + n;
 
     if (M8)
-        for (int i = threadIdx.x; i < ((n + 15) & ~15); i += blockDim.x) m8[i] = i < n ? (unsigned char)kM7Sat : 0;
-    if (threadIdx.x == 0) s_src = first;
+        for (int i = threadIdx.x; i < ((n + 15) & ~15); i += blockDim.x)
+            m8[i] = i < n ? (unsigned char)(t0 ? min(m[i], kM7Sat) : kM7Sat) : 0;
+    if (threadIdx.x == 0) s_src = t0 ? pivots[t0] : first;
     __syncthreads();
-    for (int t = 0; t < k; ++t) {
+    for (int t = t0; t < k; ++t) {
         const int src = s_src;
         if (!M8)
             for (int w = threadIdx.x; w < nbw; w += blockDim.x) bits[w] = 0u;
@@ -2322,14 +2330,14 @@ __device__ __forceinline__ void select_ell_body(int n, const int* __restrict__ r
 template <int W, bool M8>
 __global__ __launch_bounds__(kBfsBlock) void k_select_ell(int n, const int* __restrict__ rp,
                                                           const int* __restrict__ ci, const int* __restrict__ ell,
-                                                          int k, int first, int* pivots, int* m, int* gq,
+                                                          int t0, int k, int first, int* pivots, int* m, int* gq,
                                                           int* status, int wave_mode) {
-    select_ell_body<W, M8>(n, rp, ci, ell, k, first, pivots, m, gq, status, wave_mode);
+    select_ell_body<W, M8>(n, rp, ci, ell, k, first, pivots, m, gq, status, wave_mode, t0);
 }
 
 template <int W, bool M8>
-static hipError_t launch_select_ell_t(hipStream_t s, int n, const int* rp, const int* ci, const int* ell, int k,
-                                      int first, int* pivots, int* m, int* q, int* status) {
+static hipError_t launch_select_ell_t(hipStream_t s, int n, const int* rp, const int* ci, const int* ell, int t0,
+                                      int k, int first, int* pivots, int* m, int* q, int* status) {
     int threads = kBfsBlock;
     const int v = variant("select_threads");  // tuning override: 256, 512 or 1024
     if (v == 256 || v == 512) threads = v;
@@ -2337,21 +2345,114 @@ static hipError_t launch_select_ell_t(hipStream_t s, int n, const int* rp, const
     // -1 = block levels only, 2 = up to two passes)
     const int wv = variant("select_wave", 1);
     const int wave_mode = std::max(0, std::min(2, wv));
-    hipLaunchKernelGGL((k_select_ell<W, M8>), dim3(1), dim3(threads), 0, s, n, rp, ci, ell, k, first, pivots, m,
-                       q, status, wave_mode);
+    hipLaunchKernelGGL((k_select_ell<W, M8>), dim3(1), dim3(threads), 0, s, n, rp, ci, ell, t0, k, first, pivots,
+                       m, q, status, wave_mode);
     return hipGetLastError();
 }
 
 static hipError_t launch_select_ell(int W, bool m8, hipStream_t s, int n, const int* rp, const int* ci,
-                                    const int* ell, int k, int first, int* pivots, int* m, int* q, int* status) {
+                                    const int* ell, int t0, int k, int first, int* pivots, int* m, int* q,
+                                    int* status) {
     if (m8) {
-        if (W == 8) return launch_select_ell_t<8, true>(s, n, rp, ci, ell, k, first, pivots, m, q, status);
-        if (W == 16) return launch_select_ell_t<16, true>(s, n, rp, ci, ell, k, first, pivots, m, q, status);
-        return launch_select_ell_t<32, true>(s, n, rp, ci, ell, k, first, pivots, m, q, status);
+        if (W == 8) return launch_select_ell_t<8, true>(s, n, rp, ci, ell, t0, k, first, pivots, m, q, status);
+        if (W == 16) return launch_select_ell_t<16, true>(s, n, rp, ci, ell, t0, k, first, pivots, m, q, status);
+        return launch_select_ell_t<32, true>(s, n, rp, ci, ell, t0, k, first, pivots, m, q, status);
     }
-    if (W == 8) return launch_select_ell_t<8, false>(s, n, rp, ci, ell, k, first, pivots, m, q, status);
-    if (W == 16) return launch_select_ell_t<16, false>(s, n, rp, ci, ell, k, first, pivots, m, q, status);
-    return launch_select_ell_t<32, false>(s, n, rp, ci, ell, k, first, pivots, m, q, status);
+    if (W == 8) return launch_select_ell_t<8, false>(s, n, rp, ci, ell, t0, k, first, pivots, m, q, status);
+    if (W == 16) return launch_select_ell_t<16, false>(s, n, rp, ci, ell, t0, k, first, pivots, m, q, status);
+    return launch_select_ell_t<32, false>(s, n, rp, ci, ell, t0, k, first, pivots, m, q, status);
+}
+
+}  // namespace ssm
+
+#include "select_ahead.h"
+
+namespace ssm {
+
+// Searches run ahead: workers for a graph of n nodes and k pivots (0: the
+// form does not apply).
+static int ahead_workers(int n, int k) {
+    const int v = variant("select_ahead");  // override: -1 never, else the workers
+    if (v < 0 || k < 2) return 0;
+    if (v > 0) return std::min(v, sel_bits_fit(n) ? kAheadMax : kXcds);
+    return n >= kAheadMinN && k >= 8 ? kAheadWorkers : 0;
+}
+
+// The widest mean frontier (of pivot 0's BFS) with which searches run ahead:
+// twice the square root of n.  Graphs that lie in the plane (meshes, lattices,
+// geometric graphs) have 0.5 to 1.1 square roots and are foretold by distance
+// bounds; wider ones are not: a tree with 5 % extra edges (2.9 at 20k nodes)
+// took 3.9 ms instead of 2.7 ms, a preferential-attachment graph (50 at 100k
+// nodes) 8.2 instead of 3.8 ms.
+static int ahead_max_front(int n) {
+    return variant("select_ahead") > 0 ? INT_MAX : (int)(2.0 * std::sqrt((double)n));
+}
+
+template <int W, int STATE>
+static hipError_t launch_select_ahead_t(hipStream_t s, int S, int n, const int* rp, const int* ci, const int* ell,
+                                        int t0, int k, int first, int* pivots, int* m, unsigned long long* lists,
+                                        int* gq, int* marks, unsigned long long* rec, int* ctl,
+                                        unsigned long long* keys, int* status, unsigned long long* bar, int span) {
+    int max_front = ahead_max_front(n);
+    void* args[] = {&n,   &rp,  &ci,   &ell,    &t0,  &k, &first,     &pivots, &m, &lists, &gq, &marks,
+                    &rec, &ctl, &keys, &status, &bar, &S, &max_front, &span};
+    const int blocks = STATE == kAsStamps ? kAheadGroups + (kAheadMarks - 1) * kAheadMarkGroup
+                                          : (S + kAheadMarks - 1) * kXcds;
+    return hipLaunchCooperativeKernel((const void*)k_select_ahead<W, STATE>, dim3(blocks),
+                                      dim3(ahead_block(STATE)), args, 0, s);
+}
+
+// Pivots t0 .. k-1 with searches run ahead on S workers (k_select_ahead);
+// *ran stays false, with nothing enqueued, when its workspace cannot be had.
+// ecc: pivot 0's eccentricity (t0 = 1).  bar: a zeroed 64-bit barrier counter
+// for this launch alone.  *work: its workspace, for sfree once the stream is
+// idle.
+static hipError_t select_ahead(const ssm_csr* g, int S, int W, const int* ell, int t0, int ecc, int k, int first,
+                               int* pivots, int* m, unsigned long long* keys, int* status, unsigned long long* bar,
+                               void** work, bool* ran, hipStream_t s) {
+    const int n = g->n;
+    const size_t nn = ((size_t)n + 15) & ~(size_t)15;
+    const bool stamps = t0 == 1 && (!sel_bits_fit(n) || variant("select_m8") == 3);
+    const long long span = 2ll * ecc + 4;  // above any distance
+    if ((!stamps && !sel_bits_fit(n)) || (stamps && span * (k + 1ll) >= INT_MAX)) return hipSuccess;
+    const size_t lists_b = 8 * nn * (S + kAheadMarks - 1), rec_b = 16 * (size_t)kAheadRec,
+                 gq_b = (stamps ? 4 * nn * S : 8 * nn * (S + kAheadMarks - 1)), marks_b = 4 * nn * kAheadMarks;
+    if (salloc(work, lists_b + rec_b + gq_b + marks_b + 4 * kAcInts) != SSM_OK) {
+        *work = nullptr;
+        return hipSuccess;
+    }
+    *ran = true;
+    char* base = (char*)*work;
+    unsigned long long* lists = (unsigned long long*)base;
+    unsigned long long* rec = (unsigned long long*)(base + lists_b);
+    int* gq = (int*)(base + lists_b + rec_b);
+    int* marks = (int*)(base + lists_b + rec_b + gq_b);
+    int* ctl = (int*)(base + lists_b + rec_b + gq_b + marks_b);
+    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(256), 0, s, ctl, 0, (long long)kAcInts);
+    if (stamps) {  // the workers' stamps and the landmark rows, which follow them
+        const long long cnt = (long long)(gq_b + marks_b) / 4;
+        hipLaunchKernelGGL(k_fill_int, dim3(std::min(div_up(cnt, 256), 8192)), dim3(256), 0, s, gq, kInf, cnt);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const bool bytes = t0 == 0 && sel_m8_fits(n) && variant("select_m8") != 2;
+#define SSM_AHEAD(W_, ST_)                                                                                      \
+    return launch_select_ahead_t<W_, ST_>(s, S, n, g->row_ptr, g->col_idx, ell, t0, k, first, pivots, m, lists, \
+                                              gq, marks, rec, ctl, keys, status, bar, (int)span)
+    if (stamps) {
+        if (W == 8) SSM_AHEAD(8, kAsStamps);
+        if (W == 16) SSM_AHEAD(16, kAsStamps);
+        SSM_AHEAD(32, kAsStamps);
+    }
+    if (bytes) {
+        if (W == 8) SSM_AHEAD(8, kAsBytes);
+        if (W == 16) SSM_AHEAD(16, kAsBytes);
+        SSM_AHEAD(32, kAsBytes);
+    }
+    if (W == 8) SSM_AHEAD(8, kAsBits);
+    if (W == 16) SSM_AHEAD(16, kAsBits);
+    SSM_AHEAD(32, kAsBits);
+#undef SSM_AHEAD
 }
 
 template <int VW, bool ROWQ, int PRE>
@@ -2538,8 +2639,10 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
     // One workgroup: the LDS-resident form when the visited bits fit (tuning
     // override SSM_SELECT_ELL=2 keeps the global-memory form).
     int* ell = nullptr;
+    void* awork = nullptr;  // workspace of the searches run ahead
     const bool use_ell = mode == 1 && sel_bits_fit(n) && variant("select_ell") != 2;
     const int W = ell_width(g);
+    const int ahead = variant("select_mode") == 0 && variant("select_ell") != 2 ? ahead_workers(n, k) : 0;
     if (use_ell && e == hipSuccess) {
         st = salloc((void**)&ell, sizeof(int) * (size_t)n * W);
         if (st != SSM_OK) {
@@ -2551,8 +2654,18 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
         e = ell_build(g, W, ell, s);
         // with the byte copy of m when it fits (tuning override SSM_SELECT_M8=2: without)
         const bool m8 = sel_m8_fits(n) && variant("select_m8") != 2;
-        if (e == hipSuccess)
-            e = launch_select_ell(W, m8, s, n, g->row_ptr, g->col_idx, ell, k, first, pivots, m, qa, status);
+        bool ran = false;
+        if (e == hipSuccess && ahead)
+            e = select_ahead(g, ahead, W, ell, 0, 0, k, first, pivots, m, keys, status, bars, &awork, &ran, s);
+        int t0 = 0;
+        if (e == hipSuccess && ran) {
+            int hs[3] = {0, 0, 0};
+            e = hipMemcpyAsync(hs, status, sizeof hs, hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            t0 = hs[1];  // left: 1 after pivot 0, 2 during it
+        }
+        if (e == hipSuccess && (!ran || t0 != 0))
+            e = launch_select_ell(W, m8, s, n, g->row_ptr, g->col_idx, ell, t0 == 1 ? 1 : 0, k, first, pivots, m, qa, status);
     } else if (mode == 1 && e == hipSuccess) {
         e = launch_select_wg(vw, s, n, g->row_ptr, g->col_idx, k, first, pivots, m, (int2*)qa, status);
     }
@@ -2614,10 +2727,15 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
                     return st;
                 }
             } else {
+                bool ran = false;
+                if (ahead && mean_front <= ahead_max_front(n))
+                    e = select_ahead(g, ahead, W, ell, 1, hs[1], k, first, pivots, m, keys, status, bars + 16, &awork, &ran,
+                                     s);
                 int b1 = mean_front < 4096.0 ? std::min(b0, kSelGridBlocks / 2) : b0;
                 if (variant("select_blocks") > 0) b1 = std::min(gmax, variant("select_blocks"));
                 b1 = std::max(1, std::min(b1, gmax));
-                e = launch_select_grid(W, b1, s, n, g->row_ptr, g->col_idx, ell, 1, k, k, first, pivots, m, qa, qb,
+                if (e == hipSuccess && !ran)
+                    e = launch_select_grid(W, b1, s, n, g->row_ptr, g->col_idx, ell, 1, k, k, first, pivots, m, qa, qb,
                                        ctl, keys, status, bars + 16);
             }
         }
@@ -2638,6 +2756,7 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
     sfree(ws);
     sfree(keys);
     if (ell) sfree(ell);
+    if (awork) sfree(awork);
     if (e != hipSuccess) return hip_fail(e, "pivot selection");
     if (hstatus[2]) return fail(SSM_E_DEVICE, "pivot selection: a grid barrier did not fill and was aborted");
     if (hstatus[0]) return fail(SSM_E_DISCONNECTED, "graph is not connected (the first BFS missed nodes)");
