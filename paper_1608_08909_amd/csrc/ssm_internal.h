@@ -45,6 +45,7 @@ struct ssm_terms {
     int32_t* seg_owner = nullptr;  // [nseg] heavy row of each segment
     int2* seg_range = nullptr;     // [n] at a heavy node's id: its segments [x, y)
     float2* seg_sum = nullptr;     // [nseg] FP32 sweep scratch: neighbour displacement sum per segment
+    double2* heavy_sum = nullptr;  // [nheavy] FP64 sweep scratch: numerator after a heavy row's neighbours
     // Node order of the FP32 sweep (all null when off): nodes sorted by
     // (region, delta, id), so that a wavefront's nodes and their neighbours
     // lie close in memory.  The sweep runs on a renumbered copy of the graph

@@ -36,6 +36,84 @@ void launch_sum_partials(const double* partials, int count, double* out, hipStre
 
 // --------------------------------------------------------- FP64 sweep
 
+// Neighbour sums of the heavy rows (degree > kHeavyDegree) in the order of
+// k_sweep_f64, one workgroup per row: (num after the row's neighbour votes and
+// its zero-distance ones).  A single lane per row pays a square root and two
+// divisions per arc in one dependent chain (0.5 us an arc: one hub of 12,000
+// arcs held the whole sweep of a 1M-node preferential-attachment graph for
+// 6.2 ms).  Here two waves compute a chunk's votes into LDS (0 for a neighbour
+// at distance zero, which changes no sum) while one lane of each of the other
+// two adds the previous chunk's x and y in CSR order, so the chain is one
+// addition per arc.
+constexpr int kHubChunk = 512;
+
+__global__ __launch_bounds__(256) void k_heavy_f64(int nheavy, const int* __restrict__ heavy,
+                                                   const int* __restrict__ rp, const int* __restrict__ ci,
+                                                   const double2* __restrict__ xo, double2* __restrict__ hsum,
+                                                   const int* __restrict__ stop) {
+#pragma clang fp contract(off)
+    if (stop[0]) return;  // the sweep loop has met its stop test (uniform over the grid)
+    __shared__ double sv[2][2][kHubChunk];  // [buffer][x, y][arc]
+    __shared__ int s_zero;
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    for (int h = blockIdx.x; h < nheavy; h += gridDim.x) {
+        const int i = heavy[h], e0 = rp[i], e1 = rp[i + 1];
+        const double2 xv = xo[i];
+        const int chunks = (e1 - e0 + kHubChunk - 1) / kHubChunk;
+        double num = 0.0;  // lane 0 of wave 0: x; of wave 1: y
+        __syncthreads();   // the previous row's s_zero has been read
+        if (threadIdx.x == 0) s_zero = 0;
+        for (int c = 0; c <= chunks; ++c) {  // uniform: compute chunk c, add chunk c - 1
+            __syncthreads();
+            if (wave >= 2) {
+                if (c < chunks) {
+                    const int b = e0 + c * kHubChunk, m = min(kHubChunk, e1 - b);
+                    for (int q = (wave - 2) * kWave + lane; q < m; q += 2 * kWave) {
+                        const double2 xj = xo[ci[b + q]];
+                        double dx = xv.x - xj.x, dy = xv.y - xj.y;
+                        double r = sqrt(dx * dx + dy * dy);
+                        double vx = 0.0, vy = 0.0;
+                        if (r > 0.0) {
+                            vx = xj.x + dx / r;
+                            vy = xj.y + dy / r;
+                        } else {
+                            atomicAdd(&s_zero, 1);
+                        }
+                        sv[c & 1][0][q] = vx;
+                        sv[c & 1][1][q] = vy;
+                    }
+                }
+            } else if (lane == 0 && c > 0) {
+                const double* v = sv[(c - 1) & 1][wave];
+                const int m = min(kHubChunk, e1 - e0 - (c - 1) * kHubChunk);
+                int q = 0;
+                for (; q + 8 <= m; q += 8) {
+                    double t[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) t[j] = v[q + j];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) num += t[j];
+                }
+                for (; q < m; ++q) num += v[q];
+            }
+        }
+        __syncthreads();
+        if (wave < 2 && lane == 0) {
+            for (int z = s_zero; z > 0; --z) num += wave == 0 ? xv.x : xv.y;
+            ((double*)&hsum[h])[wave] = num;
+        }
+    }
+}
+
+// A heavy node's neighbour sum (k_heavy_f64); seg_range and seg_owner name its
+// place in the heavy list.
+struct HubSums {
+    const double2* sum;  // null: every row is summed by its own thread or lane group
+    const int2* seg_range;
+    const int* seg_owner;
+    __device__ __forceinline__ double2 of(int i) const { return sum[seg_owner[seg_range[i].x]]; }
+};
+
 // One thread per node.  Terms are summed exactly in the order stated by the
 // update: neighbours at a positive distance in CSR order (w = 1, d = 1), then
 // the neighbours at distance zero (each votes x_q = x_i), then pivot terms in
@@ -49,7 +127,8 @@ __global__ __launch_bounds__(256) void k_sweep_f64(int n, int kpad, int W, const
                                                    double2* __restrict__ xn, const uint4* __restrict__ dpk,
                                                    const int* __restrict__ piv,
                                                    const double* __restrict__ wt,
-                                                   const double* __restrict__ den, const int* __restrict__ stop) {
+                                                   const double* __restrict__ den, HubSums hubs,
+                                                   const int* __restrict__ stop) {
 #pragma clang fp contract(off)
     if (stop[0]) return;  // the sweep loop has met its stop test (uniform over the grid)
     extern __shared__ double2 sP[];
@@ -61,7 +140,15 @@ __global__ __launch_bounds__(256) void k_sweep_f64(int n, int kpad, int W, const
         const double xi = xv.x, yi = xv.y;
         double nx = 0.0, ny = 0.0;
         int zero = 0;
-        for (int e = rp[i]; e < rp[i + 1]; ++e) {
+        const int e0 = rp[i];
+        int e1 = rp[i + 1];
+        if (hubs.sum && e1 - e0 > kHeavyDegree) {
+            const double2 v = hubs.of(i);
+            nx = v.x;
+            ny = v.y;
+            e1 = e0;
+        }
+        for (int e = e0; e < e1; ++e) {
             const double2 xj = xo[ci[e]];
             double dx = xi - xj.x, dy = yi - xj.y;
             double r = sqrt(dx * dx + dy * dy);
@@ -111,8 +198,8 @@ __global__ __launch_bounds__(256) void k_sweep_f64(int n, int kpad, int W, const
 // group's first lane adds them in k_sweep_f64's order (neighbours in CSR
 // order, x_i once per neighbour at distance zero, pivot ranks ascending).
 // Adding an exact 0 changes no partial sum (a sum started at +0 never becomes
-// -0), so the result is k_sweep_f64's bit for bit.  Needs degree <=
-// kHeavyDegree (no heavy rows) and kpad <= kF64MaxK.
+// -0), so the result is k_sweep_f64's bit for bit.  Heavy rows start from their
+// neighbour sum (k_heavy_f64).  Needs kpad <= kF64MaxK.
 constexpr int kF64Lanes = 16;
 constexpr int kF64TermsMaxN = 65536;
 constexpr int kF64MaxK = 128;
@@ -136,7 +223,7 @@ __global__ __launch_bounds__(256) void k_sweep_f64_terms(int n, int kpad, int W,
                                                          double2* __restrict__ xn, const uint4* __restrict__ dpk,
                                                          const int* __restrict__ piv,
                                                          const double* __restrict__ wt,
-                                                         const double* __restrict__ den,
+                                                         const double* __restrict__ den, HubSums hubs,
                                                          const int* __restrict__ stop) {
 #pragma clang fp contract(off)
     if (stop[0]) return;  // the sweep loop has met its stop test (uniform over the grid)
@@ -154,12 +241,14 @@ __global__ __launch_bounds__(256) void k_sweep_f64_terms(int n, int kpad, int W,
         const int i = i0 + grp;
         double xi = 0.0, yi = 0.0;
         int e0 = 0, deg = 0;
+        bool hub = false;
         if (i < n) {
             const double2 xv = xo[i];
             xi = xv.x;
             yi = xv.y;
             e0 = rp[i];
             deg = rp[i + 1] - e0;
+            if (deg > kHeavyDegree) deg = 0, hub = true;
             for (int j = lane; j < deg; j += kF64Lanes) {
                 const double2 xj = xo[ci[e0 + j]];
                 double dx = xi - xj.x, dy = yi - xj.y;
@@ -192,6 +281,11 @@ __global__ __launch_bounds__(256) void k_sweep_f64_terms(int n, int kpad, int W,
         __syncthreads();
         if (i < n && lane == 0) {
             double nx = 0.0, ny = 0.0;
+            if (hub) {
+                const double2 v = hubs.of(i);
+                nx = v.x;
+                ny = v.y;
+            }
             for (int j = 0; j < deg; ++j) {
                 nx += T[j].x;
                 ny += T[j].y;
@@ -282,6 +376,7 @@ ssm_status heavy_segments(const ssm_csr* g, ssm_terms* t, hipStream_t s) {
     t->nseg = nseg;
     st = salloc((void**)&t->seg_owner, sizeof(int) * (size_t)std::max(nseg, 1));
     if (st == SSM_OK) st = salloc((void**)&t->seg_sum, sizeof(float2) * (size_t)std::max(nseg, 1));
+    if (st == SSM_OK) st = salloc((void**)&t->heavy_sum, sizeof(double2) * (size_t)std::max(nh, 1));
     if (st != SSM_OK) return st;
     hipLaunchKernelGGL(k_heavy_segowner, dim3(hb), dim3(256), 0, s, nh, t->heavy, t->seg_start, t->seg_owner,
                        t->seg_range);
@@ -532,6 +627,7 @@ struct SweepPlan {
     size_t lds = 0;
     bool nt = false;         // non-temporal distance loads
     bool f64_terms = false;  // FP64: k_sweep_f64_terms (small graphs)
+    bool f64_hubs = false;   // FP64: heavy rows' neighbours summed by k_heavy_f64
 };
 
 // Distance streams above half the MALL (256 MB on MI355X) are read with
@@ -586,26 +682,30 @@ static void dispatch_split(const SweepPlan& pl, hipStream_t s, const ssm_csr* g,
 // writes those of xn into pc_next.
 static void sweep_once(const SweepPlan& pl, ssm_prec p, hipStream_t s, const ssm_csr* g, const ssm_terms* t,
                        const void* xo, void* xn, const float2* pc = nullptr, float2* pc_next = nullptr) {
+    const HubSums hubs = {pl.f64_hubs ? t->heavy_sum : nullptr, t->seg_range, t->seg_owner};
+    if (p == SSM_FP64 && pl.f64_hubs)
+        hipLaunchKernelGGL(k_heavy_f64, dim3(std::min(t->nheavy, num_cus() * 8)), dim3(256), 0, s, t->nheavy, t->heavy,
+                           g->row_ptr, g->col_idx, (const double2*)xo, t->heavy_sum, t->stopw);
     if (p == SSM_FP64 && pl.f64_terms) {
         if (t->dbytes == 1)
             hipLaunchKernelGGL((k_sweep_f64_terms<uint8_t, 16>), dim3(pl.grid), dim3(256), pl.lds, s, t->n, t->kpad,
                                t->W, g->row_ptr, g->col_idx, (const double2*)xo, (double2*)xn,
-                               (const uint4*)t->dpk, t->pivots, t->wtab64, t->den64, t->stopw);
+                               (const uint4*)t->dpk, t->pivots, t->wtab64, t->den64, hubs, t->stopw);
         else
             hipLaunchKernelGGL((k_sweep_f64_terms<uint16_t, 8>), dim3(pl.grid), dim3(256), pl.lds, s, t->n, t->kpad,
                                t->W, g->row_ptr, g->col_idx, (const double2*)xo, (double2*)xn,
-                               (const uint4*)t->dpk, t->pivots, t->wtab64, t->den64, t->stopw);
+                               (const uint4*)t->dpk, t->pivots, t->wtab64, t->den64, hubs, t->stopw);
         return;
     }
     if (p == SSM_FP64) {
         if (t->dbytes == 1)
             hipLaunchKernelGGL((k_sweep_f64<uint8_t, 16>), dim3(pl.grid), dim3(pl.block), pl.lds, s, t->n, t->kpad,
                                t->W, g->row_ptr, g->col_idx, (const double2*)xo, (double2*)xn,
-                               (const uint4*)t->dpk, t->pivots, t->wtab64, t->den64, t->stopw);
+                               (const uint4*)t->dpk, t->pivots, t->wtab64, t->den64, hubs, t->stopw);
         else
             hipLaunchKernelGGL((k_sweep_f64<uint16_t, 8>), dim3(pl.grid), dim3(pl.block), pl.lds, s, t->n, t->kpad,
                                t->W, g->row_ptr, g->col_idx, (const double2*)xo, (double2*)xn,
-                               (const uint4*)t->dpk, t->pivots, t->wtab64, t->den64, t->stopw);
+                               (const uint4*)t->dpk, t->pivots, t->wtab64, t->den64, hubs, t->stopw);
         return;
     }
     if (t->nseg > 0)
@@ -660,9 +760,12 @@ static SweepPlan plan_sweep(const ssm_terms* t, ssm_prec p) {
     if (p == SSM_FP64) {
         SweepPlan pl;
         pl.block = 256;
-        // graphs up to kF64TermsMaxN nodes without heavy rows: a lane group
-        // per node (variant sweep_f64_terms -1: a thread per node)
-        pl.f64_terms = t->n <= kF64TermsMaxN && t->nheavy == 0 && t->kpad <= kF64MaxK &&
+        // the heavy list holds the ids of the FP32 sweep's order; a graph that
+        // has one has no row above 4 times the mean degree
+        pl.f64_hubs = t->nheavy > 0 && t->perm == nullptr && variant("sweep_f64_hubs") != -1;
+        // graphs up to kF64TermsMaxN nodes: a lane group per node (variant
+        // sweep_f64_terms -1: a thread per node)
+        pl.f64_terms = t->n <= kF64TermsMaxN && (t->nheavy == 0 || pl.f64_hubs) && t->kpad <= kF64MaxK &&
                        variant("sweep_f64_terms") != -1;
         if (pl.f64_terms) {
             pl.lds = f64_terms_lds(t->kpad);
