@@ -595,12 +595,36 @@ __global__ void k_ell_build(int n, int W, const int* __restrict__ rp, const int*
     }
 }
 
-// Slots per padded row: the mean degree rounded up to 8, 16 or 32.
-static int ell_width(const ssm_csr* g) {
+__global__ __launch_bounds__(256) void k_max_degree(int n, const int* __restrict__ rp, int* out) {
+    int d = 0;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+        d = max(d, rp[i + 1] - rp[i]);
+    d = wave_max(d);
+    if (lane_id() == 0 && d > 0) atomicMax(out, d);
+}
+
+// Slots per padded row: 8 for a mean degree up to 4 and wherever no row is
+// longer than 8 (a level's work goes with the slots, the unused ones too: on a
+// 150k-node mesh of degree 6 the selection takes 8.6 ms with 8 slots against
+// 10.5 ms with 16, the rows 1.7 against 2.1 ms), else 16 up to 12 and 32 above
+// (with 8 slots and rows of up to 22, a 100k-node geometric graph's selection
+// goes 9.0 -> 16.8 ms).  Synchronizes for a mean degree in (4, 8].
+static int ell_width(const ssm_csr* g, hipStream_t s) {
     const int forced = variant("ell_width");  // tuning override: 8, 16 or 32
     if (forced == 8 || forced == 16 || forced == 32) return forced;
     const double avg = g->n > 0 ? (double)g->nnz / g->n : 0.0;
-    return avg <= 4.0 ? 8 : avg <= 12.0 ? 16 : 32;
+    if (avg <= 4.0) return 8;
+    if (avg > 12.0) return 32;
+    int* d = nullptr;
+    if (avg > 8.0 || salloc((void**)&d, sizeof(int)) != SSM_OK) return 16;
+    int most = 0;
+    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, d, 0, 1ll);
+    hipLaunchKernelGGL(k_max_degree, dim3(std::min(div_up(g->n, 1024), 1024)), dim3(256), 0, s, g->n, g->row_ptr, d);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(&most, d, sizeof(int), hipMemcpyDeviceToHost, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    sfree(d);
+    return e == hipSuccess && es == hipSuccess && most <= 8 ? 8 : 16;  // an error shows in the next call on s
 }
 
 static hipError_t ell_build(const ssm_csr* g, int W, int* ell, hipStream_t s) {
@@ -997,6 +1021,8 @@ hipError_t launch_bfs_grp(int vw, int rows, hipStream_t s, int n, const int* rp,
                           int* dist, int2* queues, int* ctl, unsigned long long* bars, int* reached, int* ecc,
                           int* status);
 int bfs_grp_fits(int rows);
+static ssm_status mssp_ring(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dist, int32_t* dmax_out_host,
+                            bool* done, hipStream_t s);
 
 ssm_status mssp(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dist,
                 int32_t* dmax_out_host, hipStream_t s) {
@@ -1049,11 +1075,16 @@ ssm_status mssp(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dis
             return SSM_OK;
         }
     }
+    {
+        bool done = false;
+        ssm_status st = mssp_ring(g, k, pivots, dist, dmax_out_host, &done, s);
+        if (st != SSM_OK || done) return st;
+    }
     // LDS-resident BFS per pivot when the visited bits fit in LDS (tuning
     // override SSM_BFS_ELL=2 keeps the global-memory form).
     const int pool = bfs_ell_pool(n);
     if (pool > 0 && variant("bfs_ell") != 2 && variant("bfs_ell") != 3 && variant("bfs_ell") != 4) {
-        const int W = ell_width(g);
+        const int W = ell_width(g, s);
         const long long qcap = 1LL << 31;  // overflow ints (8 GiB)
         const int batch = (int)std::max<long long>(1, std::min<long long>(k, qcap / (3LL * n)));
         int* ell = nullptr;
@@ -1092,7 +1123,7 @@ ssm_status mssp(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dis
     // distance row as visited set; the default is the CSR form below (faster
     // on a 3.25M-node mesh: 57 against 84 ms for 100 rows without the read).
     if (variant("bfs_ell") == 3 || variant("bfs_ell") == 4) {
-        const int W = ell_width(g);
+        const int W = ell_width(g, s);
         const long long qcap = 1LL << 31;  // overflow ints (8 GiB)
         const int batch = (int)std::max<long long>(1, std::min<long long>(k, qcap / (3LL * n)));
         int* ell = nullptr;
@@ -2365,9 +2396,60 @@ static hipError_t launch_select_ell(int W, bool m8, hipStream_t s, int n, const 
 
 }  // namespace ssm
 
+#include "ring_search.h"
 #include "select_ahead.h"
 
 namespace ssm {
+
+// The k rows by k_bfs_ring.  *done stays false where the form does not apply,
+// its workspace cannot be had or a row ran out of pages; the forms of mssp then
+// run.  By default for graphs whose visited bits do not fit in LDS and whose
+// rows have at most 8 entries: 100 rows of a 3.25M-node mesh 37.3 -> 29.5 ms (37.7
+// with 16 slots per padded row, so not above).  (tuning: bfs_ring -1 = never,
+// 1 = any graph)
+static ssm_status mssp_ring(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dist, int32_t* dmax_out_host,
+                            bool* done, hipStream_t s) {
+    const int n = g->n, forced = variant("bfs_ring");
+    if (forced != 1 && (forced < 0 || sel_bits_fit(n) || variant("bfs_ell") || variant("bfs_grp") ||
+                        variant("bfs_rowq") || variant("bfs_loads") || variant("bfs_lanes")))
+        return SSM_OK;
+    if (Pages(n).count < 2 * kPagesSpare) return SSM_OK;
+    const int W = ell_width(g, s);
+    if (forced != 1 && W != 8) return SSM_OK;
+    const int batch = (int)std::max<long long>(1, std::min<long long>(k, (1LL << 31) / (2LL * n)));
+    int *ell = nullptr, *gq = nullptr, *aux = nullptr;  // aux: reached[k], ecc
+    ssm_status st = salloc((void**)&ell, sizeof(int) * (size_t)n * W);
+    if (st == SSM_OK) st = salloc((void**)&gq, sizeof(int) * 2 * (size_t)n * batch);
+    if (st == SSM_OK) st = salloc((void**)&aux, sizeof(int) * ((size_t)k + 1));
+    hipError_t e = hipSuccess;
+    std::vector<int> host((size_t)k + 1);
+    if (st == SSM_OK) {
+        e = hipMemsetAsync(aux, 0, sizeof(int) * ((size_t)k + 1), s);
+        if (e == hipSuccess) e = ell_build(g, W, ell, s);
+        for (int b0 = 0; b0 < k && e == hipSuccess; b0 += batch) {
+            auto kern = W == 8 ? k_bfs_ring<8> : W == 16 ? k_bfs_ring<16> : k_bfs_ring<32>;
+            hipLaunchKernelGGL(kern, dim3(std::min(batch, k - b0)), dim3(kBfsBlock), 0, s, n, g->row_ptr, g->col_idx,
+                               ell, pivots + b0, dist + (size_t)b0 * n, gq, aux + b0, aux + k);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(host.data(), aux, sizeof(int) * ((size_t)k + 1), hipMemcpyDeviceToHost, s);
+        (void)hipStreamSynchronize(s);  // idle before the scratch is reused
+    }
+    sfree(ell);
+    sfree(gq);
+    sfree(aux);
+    if (st == SSM_E_NOMEM && forced == 0) return SSM_OK;
+    if (st != SSM_OK) return st;
+    if (e != hipSuccess) return hip_fail(e, "multi-source BFS");
+    for (int t = 0; t < k; ++t)
+        if (host[t] < 0) return SSM_OK;
+    for (int t = 0; t < k; ++t)
+        if (host[t] != n) return fail(SSM_E_DISCONNECTED, "graph is not connected (a BFS missed nodes)");
+    *dmax_out_host = host[k];
+    *done = true;
+    return SSM_OK;
+}
 
 // Searches run ahead: workers for a graph of n nodes and k pivots (0: the
 // form does not apply).
@@ -2396,7 +2478,7 @@ static hipError_t launch_select_ahead_t(hipStream_t s, int S, int n, const int* 
     int max_front = ahead_max_front(n);
     void* args[] = {&n,   &rp,  &ci,   &ell,    &t0,  &k, &first,     &pivots, &m, &lists, &gq, &marks,
                     &rec, &ctl, &keys, &status, &bar, &S, &max_front, &span};
-    const int blocks = STATE == kAsStamps ? kAheadGroups + (kAheadMarks - 1) * kAheadMarkGroup
+    const int blocks = STATE == kRsStamps ? kAheadGroups + (kAheadMarks - 1) * kAheadMarkGroup
                                           : (S + kAheadMarks - 1) * kXcds;
     return hipLaunchCooperativeKernel((const void*)k_select_ahead<W, STATE>, dim3(blocks),
                                       dim3(ahead_block(STATE)), args, 0, s);
@@ -2440,18 +2522,18 @@ static hipError_t select_ahead(const ssm_csr* g, int S, int W, const int* ell, i
     return launch_select_ahead_t<W_, ST_>(s, S, n, g->row_ptr, g->col_idx, ell, t0, k, first, pivots, m, lists, \
                                               gq, marks, rec, ctl, keys, status, bar, (int)span)
     if (stamps) {
-        if (W == 8) SSM_AHEAD(8, kAsStamps);
-        if (W == 16) SSM_AHEAD(16, kAsStamps);
-        SSM_AHEAD(32, kAsStamps);
+        if (W == 8) SSM_AHEAD(8, kRsStamps);
+        if (W == 16) SSM_AHEAD(16, kRsStamps);
+        SSM_AHEAD(32, kRsStamps);
     }
     if (bytes) {
-        if (W == 8) SSM_AHEAD(8, kAsBytes);
-        if (W == 16) SSM_AHEAD(16, kAsBytes);
-        SSM_AHEAD(32, kAsBytes);
+        if (W == 8) SSM_AHEAD(8, kRsBytes);
+        if (W == 16) SSM_AHEAD(16, kRsBytes);
+        SSM_AHEAD(32, kRsBytes);
     }
-    if (W == 8) SSM_AHEAD(8, kAsBits);
-    if (W == 16) SSM_AHEAD(16, kAsBits);
-    SSM_AHEAD(32, kAsBits);
+    if (W == 8) SSM_AHEAD(8, kRsBits);
+    if (W == 16) SSM_AHEAD(16, kRsBits);
+    SSM_AHEAD(32, kRsBits);
 #undef SSM_AHEAD
 }
 
@@ -2641,7 +2723,7 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
     int* ell = nullptr;
     void* awork = nullptr;  // workspace of the searches run ahead
     const bool use_ell = mode == 1 && sel_bits_fit(n) && variant("select_ell") != 2;
-    const int W = ell_width(g);
+    const int W = use_ell || mode == 4 ? ell_width(g, s) : 0;
     const int ahead = variant("select_mode") == 0 && variant("select_ell") != 2 ? ahead_workers(n, k) : 0;
     if (use_ell && e == hipSuccess) {
         st = salloc((void**)&ell, sizeof(int) * (size_t)n * W);
@@ -2685,7 +2767,6 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
         // grid barrier whose time grows with the blocks, so narrow frontiers
         // (long paths, meshes) take fewer blocks (measured on MI355X: a
         // 3.25M-node mesh is fastest at 16, a 1M-node power-law graph at 32)
-        const int W = ell_width(g);
         const int gmax = std::min(select_grid_max_blocks(W), kKeysMax);
         int b0 = std::max(1, std::min(std::min(gmax, kSelGridBlocks), div_up(n, 8192)));
         st = salloc((void**)&ell, sizeof(int) * (size_t)n * W);

@@ -53,259 +53,8 @@ constexpr int kAcKnown = 0, kAcReady = 32, kAcRec = 64, kAcMask = 96, kAcLen = 1
               kAcInts = kAcGrp + 32 * (kAheadMax + kAheadMarks);
 constexpr int kAcOver = 1 << 30;  // kAcKnown once the selection has ended
 
-// How a search holds its visited set and reads m: a state byte per node in LDS
-// (bits 0-6 min(m, 127), bit 7 visited), LDS visited bits and global m,
-// visited bits alone (a landmark's full search), or, where neither fits in
-// LDS, a stamped distance per node in memory (ahead_search_grp).
-enum AheadState { kAsBytes = 0, kAsBits = 1, kAsFull = 2, kAsStamps = 3 };
-
-__host__ __device__ constexpr int ahead_pass(int state) { return state == kAsStamps ? 8 : 2; }
-__host__ __device__ constexpr int ahead_block(int state) { return state == kAsStamps ? 512 : kBfsBlock; }
-
-// Where a search's nodes go besides the frontier: the list of (node,
-// distance) pairs in order of discovery, or a full distance row.
-struct ListSink {
-    unsigned long long* p;
-    __device__ __forceinline__ void put(int at, int u, int d) const {
-        store_agent(&p[at], (unsigned long long)(unsigned)u | ((unsigned long long)(unsigned)d << 32));
-    }
-};
-struct RowSink {
-    int* p;
-    __device__ __forceinline__ void put(int, int u, int d) const { store_agent(&p[u], d); }
-};
-
-// A search's queue: the nodes in order of discovery, in LDS up to `cap`
-// entries (the rest in global memory).  A level's frontier is the stretch
-// [at, at + its size), the next one is appended behind it, so the queue is
-// also the list of the search's nodes: it goes to the sink in bulk (flush),
-// not node by node.  On gfx950 a wave's wait for a load also waits for the
-// stores it issued before, and a store that bypasses the caches takes as long
-// as a level: stored at discovery, the list cost 14 us per pivot on a
-// 100k-node geometric graph.
-constexpr int kAheadLevels = 128;  // levels between flushes at most
-
-struct RingFrontier : Frontier {
-    int cap, at, next;  // LDS entries; queue positions of the current and the next frontier
-};
-
-__device__ __forceinline__ int split(const RingFrontier& f) { return max(0, f.cap - f.at); }
-
-__device__ __forceinline__ int ring_get(const RingFrontier& f, const int* q, int pos) {
-    return pos < f.cap ? ((const __attribute__((address_space(3))) int*)q)[pos]
-                       : ((const __attribute__((address_space(1))) int*)f.gnxt)[pos - f.cap];
-}
-
-__device__ __forceinline__ void ring_set(const RingFrontier& f, int* q, int pos, int u) {
-    if (pos < f.cap)
-        q[pos] = u;
-    else
-        f.gnxt[pos - f.cap] = u;
-}
-
-__device__ __forceinline__ void put(const RingFrontier& f, int slot, int u) {
-    ring_set(f, f.lnxt, f.next + slot, u);
-}
-
-// Claims u[0..N) for distance dv; ok[j] is set where this lane claimed u[j]
-// and m lies above dv.  m is only read: it changes between the rounds.
-template <int STATE, int N>
-__device__ __forceinline__ void ahead_claim(const int (&u)[N], bool (&ok)[N], int n, unsigned* bits, const int* m,
-                                            int dv) {
-    if (STATE == kAsBytes) {
-        unsigned char* m8 = (unsigned char*)bits;
-        unsigned old[N];
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            ok[j] = (unsigned)u[j] < (unsigned)n;  // padding, continuation mark
-            old[j] = ok[j] ? atomicOr((unsigned*)(m8 + (u[j] & ~3)), 0x80u << (8 * (u[j] & 3))) : 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const unsigned ob = (old[j] >> (8 * (u[j] & 3))) & 0xffu;
-            int mv = (int)(ob & 0x7fu);
-            ok[j] = ok[j] && !(ob & 0x80u);
-            if (dv < kM7Sat) {  // uniform; a saturated byte means m >= 127 > dv
-                ok[j] = ok[j] && mv > dv;
-            } else {
-                if (ok[j] && mv >= kM7Sat) mv = load_agent(&m[u[j]]);
-                ok[j] = ok[j] && mv > dv;
-            }
-        }
-    } else {
-        int mv[N];
-        if (STATE == kAsBits) {  // m in flight beside the claims
-#pragma unroll
-            for (int j = 0; j < N; ++j) mv[j] = (unsigned)u[j] < (unsigned)n ? load_agent(&m[u[j]]) : 0;
-        }
-        claim(u, ok, bits, n);
-        if (STATE == kAsBits) {
-#pragma unroll
-            for (int j = 0; j < N; ++j) ok[j] = ok[j] && mv[j] > dv;
-        }
-    }
-}
-
-// wave_levels for a search ahead: levels whose frontier one wave covers in
-// one pass, in wave 0 alone, until the queue or the level starts ls want a
-// flush.
-template <int W, int STATE>
-__device__ __forceinline__ int ahead_wave_levels(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                                                 const int* __restrict__ ell, unsigned* bits, const int* m, int* q,
-                                                 RingFrontier& f, int len, int d0, int* ls, int& nl) {
-    constexpr int G = W / 4;
-    const int lane = lane_id(), sub = lane % G;
-    while (len > 0 && len <= wave_level_nodes<W>() && (STATE != kAsBytes || d0 + nl + 1 < kM7Sat) &&
-           nl < kAheadLevels && f.next <= f.cap / 2) {
-        const int at = f.at + lane / G;  // below cap: the frontier ends at f.next
-        const int v = lane / G < len ? q[at] : -1;
-        int4 nb = make_int4(-1, -1, -1, -1);
-        if ((unsigned)v < (unsigned)n) nb = *(const int4*)(ell + (size_t)v * W + 4 * sub);
-        const int dv = d0 + nl + 1;
-        int cnt = 0;
-        const int u[4] = {nb.x, nb.y, nb.z, nb.w};
-        bool ok[4];
-        ahead_claim<STATE>(u, ok, n, bits, m, dv);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint64_t mk = __ballot(ok[j]);
-            if (ok[j]) put(f, cnt + mask_rank(mk), u[j]);
-            cnt += __popcll(mk);
-        }
-        uint64_t hm = __ballot(sub == G - 1 && nb.w == kEllMore);
-        while (hm) {  // long rows: the whole wave over each tail, 64 arcs at a time
-            const int src_lane = __builtin_ctzll(hm);
-            hm &= hm - 1;
-            const int h = __shfl(v, src_lane);
-            const int e1 = rp[h + 1];
-            for (int e = rp[h] + W - 1 + lane; __any(e < e1); e += kWave) {
-                const int t[1] = {e < e1 ? ci[e] : -1};
-                bool okt[1];
-                ahead_claim<STATE>(t, okt, n, bits, m, dv);
-                const uint64_t mk = __ballot(okt[0]);
-                if (okt[0]) put(f, cnt + mask_rank(mk), t[0]);
-                cnt += __popcll(mk);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        len = cnt;
-        ++nl;
-        f.at = f.next;
-        f.next += cnt;
-        if (lane == 0) ls[nl] = f.at;
-    }
-    return len;
-}
-
-// BFS from src in one workgroup through the nodes whose distance lies below m
-// (kAsFull: all of them); every node found goes to the sink with its distance.
-// q: the LDS queue of cap entries, lheavy: the long-row list, bits: the
-// visited set (state bytes: flags clear on entry and on return).  gq holds
-// 2 n ints (queue overflow, long rows).  Returns the number of nodes found, or
-// -1 as soon as a frontier is wider than `widest`; ends past a barrier.
-template <int W, int STATE, class Sink>
-__device__ __forceinline__ int ahead_search(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                                            const int* __restrict__ ell, int src, int* q, int cap, int* lheavy,
-                                            unsigned* bits, const int* m, Sink sink, int* gq, int widest = INT_MAX) {
-    __shared__ int2 s_slot[3];
-    __shared__ int s_wave[4];
-    __shared__ int s_ls[kAheadLevels + 2];  // queue positions where the levels since the last flush start
-    if (STATE != kAsBytes)
-        for (int w = threadIdx.x; w < (n + 31) / 32; w += blockDim.x) bits[w] = 0u;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        if (STATE == kAsBytes)
-            ((unsigned char*)bits)[src] |= 0x80;
-        else
-            bits[src >> 5] |= 1u << (src & 31);
-        q[0] = src;
-        s_ls[0] = 0;
-        s_slot[0] = s_slot[1] = s_slot[2] = make_int2(0, 0);
-    }
-    __syncthreads();
-    RingFrontier f;
-    f.lnxt = q;
-    f.gnxt = gq;
-    f.cnt = nullptr;
-    f.lheavy = lheavy;
-    f.gheavy = gq + n;
-    f.cap = cap;
-    f.at = 0;
-    f.next = 1;
-    int total = 1, len = 1;       // nodes found; size of the current frontier
-    int base = 0, d0 = 0, nl = 0;  // flushed: nodes, levels; complete levels since
-    int step = 0;                  // block levels run: their counters rotate
-    while (len > 0) {
-        const int before = f.next;
-        if (len <= wave_level_nodes<W>() && (STATE != kAsBytes || d0 + nl + 1 < kM7Sat) && f.next <= cap / 2) {
-            if (threadIdx.x < kWave) {
-                RingFrontier g = f;
-                int l = nl;
-                const int left = ahead_wave_levels<W, STATE>(n, rp, ci, ell, bits, m, q, g, len, d0, s_ls, l);
-                if (threadIdx.x == 0) {
-                    s_wave[0] = left;
-                    s_wave[1] = l;
-                    s_wave[2] = g.at;
-                    s_wave[3] = g.next;
-                }
-            }
-            __syncthreads();
-            len = s_wave[0];
-            nl = s_wave[1];
-            f.at = s_wave[2];
-            f.next = s_wave[3];
-            __syncthreads();
-        } else {
-            level_begin(s_slot, step++, f);
-            const int dv = d0 + nl + 1, lds = split(f);
-            f.lcur = q + f.at;
-            f.gcur = gq + (lds > 0 ? 0 : f.at - cap);
-            len = ell_level_auto<W>(n, rp, ci, ell, len, f, [&](const auto& u, auto& ok) {
-                ahead_claim<STATE>(u, ok, n, bits, m, dv);
-            });
-            ++nl;
-            f.at = f.next;
-            f.next += len;
-            if (threadIdx.x == 0) s_ls[nl] = f.at;
-        }
-        total += f.next - before;
-        if (len > widest) return -1;  // uniform
-        if (len == 0 || nl >= kAheadLevels || f.next > cap / 2) {  // flush the complete levels (uniform)
-            __syncthreads();
-            for (int l = threadIdx.x / kWave; l < nl; l += blockDim.x / kWave)
-                for (int pos = s_ls[l] + lane_id(); pos < s_ls[l + 1]; pos += kWave)
-                    sink.put(base + pos, ring_get(f, q, pos), d0 + l);
-            base += f.at;
-            d0 += nl;
-            nl = 0;
-            __syncthreads();
-            for (int c = 0; c < len; c += blockDim.x) {  // the current frontier to the front
-                const int i = c + (int)threadIdx.x;
-                const int u = i < len ? ring_get(f, q, f.at + i) : 0;
-                __syncthreads();
-                if (i < len) ring_set(f, q, i, u);
-                __syncthreads();
-            }
-            f.at = 0;
-            f.next = len;
-            if (threadIdx.x == 0) s_ls[0] = 0;
-            __syncthreads();
-        }
-    }
-    if (STATE == kAsBytes) {
-        uint4* w16 = (uint4*)bits;
-        for (int w = threadIdx.x; w < (n + 15) / 16; w += blockDim.x) {
-            uint4 x = w16[w];
-            x.x &= 0x7f7f7f7fu;
-            x.y &= 0x7f7f7f7fu;
-            x.z &= 0x7f7f7f7fu;
-            x.w &= 0x7f7f7f7fu;
-            w16[w] = x;
-        }
-    }
-    __syncthreads();
-    return total;
-}
+__host__ __device__ constexpr int ahead_pass(int state) { return state == kRsStamps ? 8 : 2; }
+__host__ __device__ constexpr int ahead_block(int state) { return state == kRsStamps ? 512 : kBfsBlock; }
 
 // The same search by a group of G workgroups, for graphs whose visited bits do
 // not fit in LDS: the levels of k_select_grid, with the list itself as the
@@ -410,7 +159,7 @@ __device__ __forceinline__ int ahead_search_grp(int n, const int* __restrict__ r
 //
 // One workgroup per worker: all of them on XCD 0 (workgroups go to the XCDs in
 // turn, the others leave at once), so that the rows one search read are in the
-// L2 of the next (5 % on a 150k-node mesh).  With groups (kAsStamps) the
+// L2 of the next (5 % on a 150k-node mesh).  With groups (kRsStamps) the
 // kAheadGroups workgroups divide evenly over a round's searches (the early
 // ones, wide and not foretold, get kAheadGroupMax), and the pivot's own search
 // lowers m itself, as k_select_grid does.  The searches beside it then see m
@@ -425,7 +174,7 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
     constexpr int kBlk = ahead_block(STATE);
     constexpr int R = 8;            // records per thread
     constexpr int kRec = R * kBlk;  // records kept per round
-    __shared__ __align__(16) unsigned char pool[STATE == kAsStamps ? 4 * ((ahead_pass(STATE) + 1) * kBlk + kAheadIds) : kSelPool];
+    __shared__ __align__(16) unsigned char pool[STATE == kRsStamps ? 4 * ((ahead_pass(STATE) + 1) * kBlk + kAheadIds) : kSelPool];
     __shared__ unsigned long long s_red[kBlk / kWave];
     __shared__ int s_cid[kAheadMax], s_clen[kAheadMax];  // per worker: the candidate searched, its list's length
     __shared__ int s_cand[kAheadMax];
@@ -436,12 +185,12 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
     unsigned* bits = (unsigned*)(lheavy + kHeavyCap);
     unsigned char* m8 = (unsigned char*)bits;
     // the visited set's bytes, then the queue (the rest of the pool, at least 4096 ints)
-    const int set_bytes = STATE == kAsStamps ? 0 : STATE == kAsBytes ? (n + 15) & ~15 : ((n + 31) / 32 * 4 + 15) & ~15;
-    int* lq = STATE == kAsStamps ? (int*)pool : (int*)((unsigned char*)bits + set_bytes);
+    const int set_bytes = STATE == kRsStamps ? 0 : STATE == kRsBytes ? (n + 15) & ~15 : ((n + 31) / 32 * 4 + 15) & ~15;
+    int* lq = STATE == kRsStamps ? (int*)pool : (int*)((unsigned char*)bits + set_bytes);
     const int cap = (kSelPool - 4 * kHeavyCap - set_bytes) / 4;
     const int tid = threadIdx.x;
     // NB workgroups are the workers', b is this one's rank; then come the landmarks'
-    constexpr bool kGroups = STATE == kAsStamps;
+    constexpr bool kGroups = STATE == kRsStamps;
     if (!kGroups && blockIdx.x % kXcds != 0) return;
     const int b = kGroups ? blockIdx.x : blockIdx.x / kXcds, NB = kGroups ? kAheadGroups : S;
     const bool lead = b == 0 && tid == 0;
@@ -467,7 +216,7 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
         const int src = s_n;
         if (src < 0) return;
         int* row = marks + (size_t)f * n;
-        if constexpr (STATE == kAsStamps) {  // the row is its own stamps, infinite on entry
+        if constexpr (STATE == kRsStamps) {  // the row is its own stamps, infinite on entry
             unsigned long long* list = lists + (size_t)(S + f - 1) * n;
             if (member == 0 && tid == 0) {
                 store_agent(&row[src], 0);
@@ -479,7 +228,7 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
                 0)
                 return;
         } else {
-            ahead_search<W, kAsFull>(n, rp, ci, ell, src, lq, cap, lheavy, bits, m, RowSink{row}, myq);
+            ring_search<W, kRsFull>(n, rp, ci, ell, src, lq, cap, lheavy, bits, m, RowSink{row}, myq);
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
         }
@@ -501,7 +250,7 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
     const int lo = (int)min((long long)n, (long long)b * per), hi = min(n, lo + per);
     // value of node i from this worker's state
     auto value = [&](int i) {
-        if (STATE == kAsBytes) {
+        if (STATE == kRsBytes) {
             const int b = m8[i] & 0x7f;
             if (b < kM7Sat) return b;
         }
@@ -511,7 +260,7 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
         s_cid[tid] = -1;
         s_runs[tid] = 0;
     }
-    if (STATE == kAsBytes)
+    if (STATE == kRsBytes)
         for (int i = tid; i < ((n + 15) & ~15); i += blockDim.x) m8[i] = i < n ? (unsigned char)kM7Sat : 0;
     int p = t0 == 0 ? first : load_agent(&pivots[1]);
     int top = kInf;  // m[p]
@@ -737,7 +486,7 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
                 __syncthreads();
                 if (tid < S && (fresh >> tid & 1)) ++s_runs[tid];
             } else if (fresh >> b & 1) {
-                const int len = ahead_search<W, STATE>(n, rp, ci, ell, s_cid[b], lq, cap, lheavy, bits, m,
+                const int len = ring_search<W, STATE>(n, rp, ci, ell, s_cid[b], lq, cap, lheavy, bits, m,
                                                        ListSink{lists + (size_t)b * n}, myq,
                                                        t == 0 && max_front < INT_MAX / 2 ? 2 * max_front : INT_MAX);
                 if (tid == 0) store_agent(&ctl[kAcLen + b], len);
@@ -772,12 +521,12 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
                 atomicMin(&m[v], d);
                 if (t == 0) store_agent(&marks[v], d);
             }
-            if (STATE == kAsBytes) {
+            if (STATE == kRsBytes) {
                 const int b = m8[v];
                 if (d < b) m8[v] = (unsigned char)d;  // d < 127 here
             }
         };
-        if (STATE == kAsBytes) {
+        if (STATE == kRsBytes) {
             for (int q0 = tid; q0 < len; q0 += 4 * kBlk) {
                 unsigned long long e[4];
 #pragma unroll
@@ -795,13 +544,13 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
         }
         if (t == 0 && lead) atomicOr(&ctl[kAcReady], 1);  // complete at the barrier, used after it
         // state bytes are this worker's own; only values of 127 and above are read from the shared m
-        if (STATE != kAsBytes || top >= kM7Sat)
+        if (STATE != kRsBytes || top >= kM7Sat)
             SYNC_OR_LEAVE();
         else
             __syncthreads();
         // argmax of m, each worker over its slice
         unsigned long long best = 0;
-        if (STATE == kAsBytes) {
+        if (STATE == kRsBytes) {
             const uint4* w16 = (const uint4*)(m8 + lo);
             int bv = -1, bi = 0;
             for (int q = tid; q < (hi - lo + 15) / 16; q += blockDim.x) {
