@@ -62,7 +62,10 @@ ssm_status salloc(void** p, size_t bytes) {
     *p = nullptr;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    bytes = std::max<size_t>(bytes, 16);
+    // compared and allocated in whole grains: by the bytes asked for, no cached
+    // buffer (2 MiB at least) would serve a request below 512 KiB, and every
+    // small request would allocate anew (a 2,500-node layout makes about 20)
+    bytes = std::max<size_t>(1, (bytes + kScratchGrain - 1) / kScratchGrain) * kScratchGrain;
     std::lock_guard<std::mutex> lock(g_scratch_mu);
     int best = -1;
     for (int q = 0; q < (int)g_scratch_free.size(); ++q) {
@@ -79,10 +82,9 @@ ssm_status salloc(void** p, size_t bytes) {
         *p = b.p;
         return SSM_OK;
     }
-    const size_t rounded = (bytes + kScratchGrain - 1) / kScratchGrain * kScratchGrain;
-    ssm_status st = dalloc(p, rounded);
+    ssm_status st = dalloc(p, bytes);
     if (st != SSM_OK) return st;
-    g_scratch_live[*p] = CachedBlock{dev, *p, rounded};
+    g_scratch_live[*p] = CachedBlock{dev, *p, bytes};
     return SSM_OK;
 }
 
