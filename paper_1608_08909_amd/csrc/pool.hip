@@ -275,6 +275,57 @@ inline int pool_hist_mode(int kpad, int L, int W) {
     return sizeof(float) * (size_t)kpad * L + sizeof(float2) * (size_t)W <= (size_t)kPoolHistLds;
 }
 
+// The pivot terms of one node in a pooled FP32 sweep, ascending rank; (wa, wb)
+// are its first two packed words.  HIST: from the LDS tables sInv and sH, else
+// from the global (w', w' d) table.  The two forms are loops of their own and
+// no read waits behind a branch: with the choice made inside the loop every
+// term waited for its own reads and for the packed words in flight.  A sweep
+// of 96 graphs of about 9700 nodes, k = 95 to 100: 72 us so, 69 us with the
+// tables staged by 16-byte loads, 63 us with the loops apart; 20 vector
+// instructions a term (most of that time) bound it now.  Blocks of 512 and 1024
+// nodes, which stage the tables less often, took 66 and 75 us.
+template <bool HIST>
+__device__ __forceinline__ void pool_terms(const PoolGraph& g, int n, int nwords, float2 xi,
+                                           const float2* __restrict__ sP, const float2* __restrict__ sInv,
+                                           const float* __restrict__ sH, const uint4* __restrict__ dp, uint4 wa,
+                                           uint4 wb, float& ax, float& ay) {
+    const float tiny = 1e-30f;
+    const int L = g.L, W = g.W;
+    const float2* __restrict__ wt2 = g.wt2;
+    for (int b = 0; b < nwords; ++b) {
+        union {
+            uint4 v;
+            uint16_t e[8];
+        } u;
+        u.v = wa;
+        wa = wb;
+        if (b + 2 < nwords) wb = dp[(size_t)(b + 2) * n];  // two words ahead
+        float2 c[8], pv[8];
+        float h[8];
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+            const int t = b * 8 + jj;
+            const int d = (int)u.e[jj];
+            if (HIST) {
+                h[jj] = sH[t * L + min(d >> 1, L - 1)];
+                c[jj] = sInv[d];
+            } else {
+                c[jj] = wt2[(size_t)t * W + d];
+            }
+            pv[jj] = sP[t];
+        }
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+            const float dx = pv[jj].x - xi.x, dy = pv[jj].y - xi.y;
+            const float inv = __builtin_amdgcn_rsqf(dx * dx + (dy * dy + tiny));
+            float f = fmaf(-c[jj].y, inv, c[jj].x);
+            if (HIST) f *= h[jj];
+            ax += f * dx;
+            ay += f * dy;
+        }
+    }
+}
+
 // FP32 sweep s of a call on one 256-node chunk ch = (graph, first node) of
 // one graph, by a block of 256 threads (thread = node).  A graph takes part
 // while s < its iters; it reads x32[(parity + s) & 1] and writes the other
@@ -299,19 +350,23 @@ __device__ __forceinline__ void pool_sweep_chunk(const PoolGraph* __restrict__ g
     }
     float2* sP = (float2*)psm;                   // [kpad]
     float2* sInv = sP + kpad;                    // [W] (hist)
-    float* sH = (float*)(sInv + (hist ? W : 0));  // [kpad][L] (hist)
+    float* sH = (float*)(sInv + (hist ? (W + 1) / 2 * 2 : 0));  // [kpad][L] (hist), 16-byte aligned
+    // the node's own loads in flight beside the staging's
+    const int i = ch.y + threadIdx.x, ic = min(i, n - 1);
+    const float2 xi = xo[ic];
+    const int e0 = g.rp[ic], e1 = g.rp[ic + 1];
+    const uint4* __restrict__ dp = g.dpk + ic;
+    uint4 wa = nwords > 0 ? dp[0] : make_uint4(0, 0, 0, 0);
+    uint4 wb = nwords > 1 ? dp[(size_t)n] : make_uint4(0, 0, 0, 0);
     for (int t = threadIdx.x; t < kpad; t += blockDim.x) sP[t] = xo[g.pivots[t]];
     if (hist) {
-        for (int d = threadIdx.x; d < W; d += blockDim.x) sInv[d] = g.invd[d];
-        for (int q = threadIdx.x; q < kpad * L; q += blockDim.x) sH[q] = g.Hf[q];
+        stage_lds(sInv, g.invd, sizeof(float2) * (size_t)W);
+        stage_lds(sH, g.Hf, sizeof(float) * (size_t)kpad * L);
     }
     __syncthreads();
-    const int i = ch.y + threadIdx.x;
     if (i >= n) return;
     const float tiny = 1e-30f;
-    const float2 xi = xo[i];
     float ax = 0.f, ay = 0.f;
-    const int e0 = g.rp[i], e1 = g.rp[i + 1];
     for (int e = e0; e < e1; e += 4) {
         int j[4];
 #pragma unroll
@@ -331,37 +386,10 @@ __device__ __forceinline__ void pool_sweep_chunk(const PoolGraph* __restrict__ g
             ay += f * dy;
         }
     }
-    const uint4* __restrict__ dp = g.dpk + i;
-    uint4 wa = nwords > 0 ? dp[0] : make_uint4(0, 0, 0, 0);
-    uint4 wb = nwords > 1 ? dp[(size_t)n] : make_uint4(0, 0, 0, 0);
-    for (int b = 0; b < nwords; ++b) {
-        union {
-            uint4 v;
-            uint16_t e[8];
-        } u;
-        u.v = wa;
-        wa = wb;
-        if (b + 2 < nwords) wb = dp[(size_t)(b + 2) * n];  // two words ahead
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-            const int t = b * 8 + jj;
-            const int d = (int)u.e[jj];
-            const float2 pv = sP[t];
-            const float dx = pv.x - xi.x, dy = pv.y - xi.y;
-            const float inv = __builtin_amdgcn_rsqf(dx * dx + (dy * dy + tiny));
-            float f;
-            if (hist) {
-                const float h = sH[t * L + min(d >> 1, L - 1)];
-                const float2 id = sInv[d];
-                f = fmaf(-id.y, inv, id.x) * h;
-            } else {
-                const float2 f01 = g.wt2[(size_t)t * W + d];
-                f = fmaf(-f01.y, inv, f01.x);
-            }
-            ax += f * dx;
-            ay += f * dy;
-        }
-    }
+    if (hist)
+        pool_terms<true>(g, n, nwords, xi, sP, sInv, sH, dp, wa, wb, ax, ay);
+    else
+        pool_terms<false>(g, n, nwords, xi, sP, sInv, sH, dp, wa, wb, ax, ay);
     const float dn = g.den32[i];
     xn[i] = make_float2(xi.x + ax / dn, xi.y + ay / dn);
 }
@@ -892,9 +920,9 @@ ssm_status ssm_pool_add(ssm_pool* p, int32_t n, int32_t nnz, const int32_t* row_
     }
     s.state = kAdded;
     bind(p, s);
-    hipError_t e = hipMemcpyAsync((void*)s.g.rp, row_ptr_host, sizeof(int) * (n + 1), hipMemcpyHostToDevice, stream);
+    hipError_t e = hipMemcpyAsync(const_cast<int*>((const int*)s.g.rp), row_ptr_host, sizeof(int) * (n + 1), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess && nnz > 0)
-        e = hipMemcpyAsync((void*)s.g.ci, col_idx_host, sizeof(int) * (size_t)nnz, hipMemcpyHostToDevice, stream);
+        e = hipMemcpyAsync(const_cast<int*>((const int*)s.g.ci), col_idx_host, sizeof(int) * (size_t)nnz, hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) {
         p->arena.release(s.off_p, s.sz_p);
@@ -1126,7 +1154,7 @@ ssm_status ssm_pool_sweep(ssm_pool* p, int32_t count, const int32_t* slots, int3
         first.push_back((int)stg.hc.size());
         for (int i0 = 0; i0 < sl.n; i0 += kPoolSweepBlock) stg.hc.push_back(make_int2(q, i0));
         lds = std::max(lds, sizeof(float2) * (size_t)sl.kpad +
-                                (g.hist ? sizeof(float2) * (size_t)g.W + sizeof(float) * (size_t)sl.kpad * g.L : 0));
+                                (g.hist ? sizeof(float2) * (((size_t)g.W + 1) / 2 * 2) + sizeof(float) * (size_t)sl.kpad * g.L : 0));
     }
     if (most == 0) return SSM_OK;
     first.push_back((int)stg.hc.size());

@@ -73,30 +73,6 @@ __global__ __launch_bounds__(256) void k_heavy_edges(int nseg, const int* __rest
     }
 }
 
-// Copies nbytes (a multiple of 4) from global to LDS with 16-byte loads,
-// four in flight per thread (both sides 16-byte aligned).  The loads are
-// unconditional (an index past the end rereads the last word) so that they
-// stay in registers and issue together; only the LDS stores are guarded.
-__device__ __forceinline__ void stage_lds(void* dst, const void* __restrict__ src, size_t nbytes) {
-    const int n16 = (int)(nbytes / 16);
-    const int step = blockDim.x;
-    uint4* d = (uint4*)dst;
-    const uint4* g = (const uint4*)src;
-    for (int q0 = threadIdx.x; q0 < n16; q0 += 4 * step) {
-        const int last = n16 - 1;
-        const uint4 v0 = g[q0];
-        const uint4 v1 = g[min(q0 + step, last)];
-        const uint4 v2 = g[min(q0 + 2 * step, last)];
-        const uint4 v3 = g[min(q0 + 3 * step, last)];
-        d[q0] = v0;
-        if (q0 + step < n16) d[q0 + step] = v1;
-        if (q0 + 2 * step < n16) d[q0 + 2 * step] = v2;
-        if (q0 + 3 * step < n16) d[q0 + 3 * step] = v3;
-    }
-    for (int q = 4 * n16 + threadIdx.x; q < (int)(nbytes / 4); q += step)
-        ((unsigned*)dst)[q] = ((const unsigned*)src)[q];
-}
-
 // Block = CPB groups of SPLIT wavefronts; a group takes 64 consecutive nodes
 // (lane = node) and its SPLIT waves share the node's terms.  The terms are
 // summed in four classes by packed-word index b mod 4, each class in
