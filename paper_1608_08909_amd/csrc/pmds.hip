@@ -1257,49 +1257,44 @@ ssm_status pivotmds(const ssm_csr* g, ssm_terms* t, ssm_prec p, void* x, hipStre
 
 // ------------------------------------------------------------ layout pool
 
-// Per graph: colsum, mu, gamma and nu from its distance rows (the same exact
-// integer sums and the same divisions as the single-graph path).
-__global__ __launch_bounds__(1024) void k_pool_mds_stats(const PoolGraph* __restrict__ gs) {
-    const PoolGraph& g = gs[blockIdx.x];
-    const int n = g.n, k = g.k;
-    __shared__ long long red[1024 / kWave];
-    constexpr int U = 8;  // rows per pass (exact integer sums: any order)
-    for (int t0 = 0; t0 < k; t0 += U) {
-        long long s[U];
+// Block (x, graph): colsum and mu of 8 ranks from the graph's distance rows
+// (the same exact integer sums and the same divisions as the single-graph
+// path).  One workgroup per graph for all ranks took 0.65 ms for 96 graphs of
+// about 9700 nodes, these blocks and k_pool_gamma take 0.13 ms.
+constexpr int kStatRows = 8;
+__global__ __launch_bounds__(256) void k_pool_mds_stats(const PoolGraph* __restrict__ gs) {
+    const PoolGraph& g = gs[blockIdx.y];
+    const int n = g.n, k = g.k, t0 = blockIdx.x * kStatRows;
+    if (t0 >= k) return;  // the whole block
+    __shared__ long long red[256 / kWave];
+    long long s[kStatRows];
 #pragma unroll
-        for (int j = 0; j < U; ++j) s[j] = 0;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            long long d[U];
-#pragma unroll
-            for (int j = 0; j < U; ++j) d[j] = t0 + j < k ? g.dist[(size_t)(t0 + j) * n + i] : 0;
-#pragma unroll
-            for (int j = 0; j < U; ++j) s[j] += d[j] * d[j];
-        }
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const long long v = block_sum(s[j], red);
-            if (threadIdx.x == 0 && t0 + j < k) g.colsum[t0 + j] = v;
-        }
-    }
-    if (threadIdx.x == 0) {  // colsum was written by this thread
-        long long total = 0;
-        for (int t = 0; t < k; ++t) {
-            g.mu[t] = (double)g.colsum[t] / (double)n;
-            total += g.colsum[t];
-        }
-        g.stats[0] = (double)total / ((double)n * (double)k);
-    }
+    for (int j = 0; j < kStatRows; ++j) s[j] = 0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        long long s = 0;
-        for (int t0 = 0; t0 < k; t0 += U) {
-            long long d[U];
+        long long d[kStatRows];
 #pragma unroll
-            for (int j = 0; j < U; ++j) d[j] = t0 + j < k ? g.dist[(size_t)(t0 + j) * n + i] : 0;
+        for (int j = 0; j < kStatRows; ++j) d[j] = t0 + j < k ? g.dist[(size_t)(t0 + j) * n + i] : 0;
 #pragma unroll
-            for (int j = 0; j < U; ++j) s += d[j] * d[j];
-        }
-        g.nu[i] = (double)s / (double)k;
+        for (int j = 0; j < kStatRows; ++j) s[j] += d[j] * d[j];
     }
+#pragma unroll
+    for (int j = 0; j < kStatRows; ++j) {
+        const long long v = block_sum(s[j], red);
+        if (threadIdx.x == 0 && t0 + j < k) {
+            g.colsum[t0 + j] = v;
+            g.mu[t0 + j] = (double)v / (double)n;
+        }
+    }
+}
+
+// One wave per graph: gamma.
+__global__ __launch_bounds__(kWave) void k_pool_gamma(const PoolGraph* __restrict__ gs) {
+    const PoolGraph& g = gs[blockIdx.x];
+    const int k = g.k;
+    long long total = 0;
+    for (int t = threadIdx.x; t < k; t += kWave) total += g.colsum[t];
+    for (int d = kWave / 2; d; d >>= 1) total += __shfl_xor(total, d);
+    if (threadIdx.x == 0) g.stats[0] = (double)total / ((double)g.n * (double)k);
 }
 
 // Items (graph, node chunk, tile group): the Gram partial tiles.
@@ -1407,7 +1402,8 @@ __global__ __launch_bounds__(1024) void k_pool_project(const PoolGraph* __restri
 
 hipError_t pool_pivotmds(const PoolGraph* gs, int count, const int4* gram_items, int ngram, const int2* tiles,
                          int kp_max, int k_max, hipStream_t s) {
-    hipLaunchKernelGGL(k_pool_mds_stats, dim3(count), dim3(1024), 0, s, gs);
+    hipLaunchKernelGGL(k_pool_mds_stats, dim3(div_up(k_max, kStatRows), count), dim3(256), 0, s, gs);
+    hipLaunchKernelGGL(k_pool_gamma, dim3(count), dim3(kWave), 0, s, gs);
     // rounds of 32 nodes when the batch's largest staged block fits 64 KB (kPoolGramChunk is a multiple of 32)
     if (gram_sub(kp_max) == 32)
         hipLaunchKernelGGL(k_pool_gram<32>, dim3(ngram), dim3(256), gram_lds_bytes<32>(kp_max), s, gs, gram_items,
