@@ -2216,7 +2216,8 @@ __device__ __forceinline__ int wave_levels(int n, const int* __restrict__ rp, co
 template <int W, bool M8, int SPOOL = kSelPool>
 __device__ __forceinline__ void select_ell_body(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                 const int* __restrict__ ell, int k, int first, int* pivots, int* m,
-                                                int* gq, int* status, int wave_mode = 1, int t0 = 0) {
+                                                int* gq, int* status, int wave_mode = 1, int t0 = 0,
+                                                int* pub = nullptr, int* ready = nullptr) {
     __shared__ __align__(16) unsigned char pool[SPOOL];
     __shared__ int2 s_slot[3];
     __shared__ int s_src;
@@ -2244,6 +2245,10 @@ __device__ __forceinline__ void select_ell_body(int n, const int* __restrict__ r
         __syncthreads();
         if (threadIdx.x == 0) {
             pivots[t] = src;
+            if (pub) {
+                __hip_atomic_store(pub + t, src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(ready, t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
             m[src] = 0;
             if (M8)
                 m8[src] = 0x80;  // m = 0, visited
@@ -2352,6 +2357,10 @@ __device__ __forceinline__ void select_ell_body(int n, const int* __restrict__ r
         if (threadIdx.x == 0) {
             if (t == 0 && (int)(best >> 32) == kInf) status[0] = 1;
             s_src = (int)(0xffffffffu - (unsigned)(best & 0xffffffffu));
+            if (pub && t == 0 && (int)(best >> 32) == kInf) {  // the unset ranks name node 0
+                for (int r = 1; r < k; ++r) __hip_atomic_store(pub + r, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(ready, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
         __syncthreads();
         if (t == 0 && (int)(best >> 32) == kInf) break;  // disconnected (uniform)
@@ -3291,17 +3300,33 @@ constexpr int kPoolSelS = kLdsFixed + 22528, kPoolSelL = kLdsFixed + kPoolMaxN;
 constexpr int kPoolSelBlock = 512;
 constexpr int kPoolBfsBlock = 256;
 
-template <int SPOOL>
-__global__ __launch_bounds__(kPoolSelBlock) void k_pool_select(const PoolGraph* __restrict__ gs) {
+// What the searches that follow the selections of a batch share with them:
+// per graph the ranks published (ready), the ranks taken (taken) and the first
+// of its entries in pub; per graph and rank the pivot (-1: not yet).
+struct PoolFollow {
+    int *ready, *taken, *first, *pub;
+    __device__ PoolFollow(int* p, int count) : ready(p), taken(p + count), first(p + 2 * count), pub(p + 3 * count) {}
+};
+
+// Whether a batch's searches follow its selections: while every selection has
+// a CU of its own, the rest of the device is idle beside them.  (tuning:
+// pool_follow -1 = never)
+bool pool_follows(int count) { return count <= num_cus() && variant("pool_follow") >= 0; }
+
+template <int SPOOL, bool PUB>
+__global__ __launch_bounds__(kPoolSelBlock) void k_pool_select(const PoolGraph* __restrict__ gs, int* follow) {
     const PoolGraph& g = gs[blockIdx.x];
-    select_ell_body<kPoolEllW, true, SPOOL>(g.n, g.rp, g.ci, g.ell, g.k, g.first, g.pivots, g.m, g.gq, g.info);
+    const PoolFollow f(follow, gridDim.x);  // read with PUB alone
+    select_ell_body<kPoolEllW, true, SPOOL>(g.n, g.rp, g.ci, g.ell, g.k, g.first, g.pivots, g.m, g.gq, g.info, 1, 0,
+                                            PUB ? f.pub + f.first[blockIdx.x] : nullptr,
+                                            PUB ? f.ready + blockIdx.x : nullptr);
 }
 
-hipError_t pool_select(const PoolGraph* gs, int count, int nmax, hipStream_t s) {
-    if (kLdsFixed + (((size_t)nmax + 15) & ~(size_t)15) <= (size_t)kPoolSelS)
-        hipLaunchKernelGGL(k_pool_select<kPoolSelS>, dim3(count), dim3(kPoolSelBlock), 0, s, gs);
-    else
-        hipLaunchKernelGGL(k_pool_select<kPoolSelL>, dim3(count), dim3(kPoolSelBlock), 0, s, gs);
+hipError_t pool_select(const PoolGraph* gs, int count, int nmax, int* follow, hipStream_t s) {
+    const bool small = kLdsFixed + (((size_t)nmax + 15) & ~(size_t)15) <= (size_t)kPoolSelS;
+    auto kern = follow ? (small ? k_pool_select<kPoolSelS, true> : k_pool_select<kPoolSelL, true>)
+                       : (small ? k_pool_select<kPoolSelS, false> : k_pool_select<kPoolSelL, false>);
+    hipLaunchKernelGGL(kern, dim3(count), dim3(kPoolSelBlock), 0, s, gs, follow);
     return hipGetLastError();
 }
 
@@ -3321,6 +3346,80 @@ __global__ __launch_bounds__(kPoolBfsBlock) void k_pool_bfs(const PoolGraph* __r
         bfs_ell_body<kPoolEllW, kPoolS>(g.n, g.rp, g.ci, g.ell, g.pivots[st.y], g.dist + (size_t)st.y * g.n, myq,
                                          &s_reached, g.info + 1);
     }
+}
+
+// The BFS of the batch's pivots as they are published: a block takes the next
+// rank of any graph that has one ready, and runs it as k_pool_bfs does.  Run
+// twice: beside the selections, where a block with nothing to take looks again
+// `looks` times in all and then ends (so the launch ends whatever becomes of
+// the selections), and after both, with looks = 0, for the ranks left.  A rank
+// taken is always done by its taker, so those left are taken[q] .. k - 1.
+// Blocks begin to look at different graphs.  96 graphs of about 9700 nodes, k =
+// 95 to 100: selections 4.7 ms, then 9600 BFS 3.8 ms; so, the whole call took
+// 30.9 ms instead of 33.6 (with 2 following blocks per CU; 33.3 with 1, 31.5
+// with 3, 32.4 with 4, which slow the selections).
+__global__ __launch_bounds__(kPoolBfsBlock) void k_pool_bfs_follow(const PoolGraph* __restrict__ gs, int count,
+                                                                   int* follow, int looks, int* gq,
+                                                                   long long gq_stride) {
+    __shared__ int s_reached, s_pick, s_open, s_rank, s_src;
+    const PoolFollow f(follow, count);
+    int* myq = gq + (size_t)blockIdx.x * gq_stride;
+    const int start = (int)((blockIdx.x * 37u) % (unsigned)count);
+    for (;;) {
+        __syncthreads();  // the previous round's reads of LDS are done
+        if (threadIdx.x == 0) {
+            s_pick = INT_MAX;
+            s_open = 0;
+            s_rank = -1;
+        }
+        __syncthreads();
+        for (int j = threadIdx.x; j < count; j += blockDim.x) {
+            const int q = start + j < count ? start + j : start + j - count;
+            const int a = __hip_atomic_load(f.taken + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int r = __hip_atomic_load(f.ready + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (a < r) atomicMin(&s_pick, j);
+            if (a < gs[q].k) s_open = 1;
+        }
+        __syncthreads();
+        const int pick = s_pick, open = s_open;
+        if (!open) return;  // the whole block
+        if (pick == INT_MAX) {
+            if (looks-- <= 0) return;  // the whole block
+            __builtin_amdgcn_s_sleep(32);
+            continue;
+        }
+        const int q = start + pick < count ? start + pick : start + pick - count;
+        if (threadIdx.x == 0) {
+            const int r = __hip_atomic_load(f.ready + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            int a = __hip_atomic_load(f.taken + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            while (a < r && !__hip_atomic_compare_exchange_strong(f.taken + q, &a, a + 1, __ATOMIC_RELAXED,
+                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+            }
+            if (a < r) {
+                // its store was issued before that of `ready`, which has been
+                // seen: it arrives without anybody's doing
+                int v;
+                while ((v = __hip_atomic_load(f.pub + f.first[q] + a, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT)) < 0)
+                    __builtin_amdgcn_s_sleep(1);
+                s_rank = a;
+                s_src = v;
+            }
+        }
+        __syncthreads();
+        const int rank = s_rank;
+        if (rank < 0) continue;  // the whole block
+        const PoolGraph& g = gs[q];
+        bfs_ell_body<kPoolEllW, kPoolS>(g.n, g.rp, g.ci, g.ell, s_src, g.dist + (size_t)rank * g.n, myq, &s_reached,
+                                         g.info + 1);
+    }
+}
+
+hipError_t pool_bfs_follow(const PoolGraph* gs, int count, int* follow, int looks, int* gq, long long gq_stride,
+                           int blocks, hipStream_t s) {
+    hipLaunchKernelGGL(k_pool_bfs_follow, dim3(blocks), dim3(kPoolBfsBlock), 0, s, gs, count, follow, looks, gq,
+                       gq_stride);
+    return hipGetLastError();
 }
 
 int pool_bfs_blocks(int nitems) { return std::max(1, std::min(nitems, 5 * num_cus())); }

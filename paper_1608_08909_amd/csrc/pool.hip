@@ -710,6 +710,9 @@ ssm_status wait_all(ssm_pool* p) {
     return SSM_OK;
 }
 
+constexpr int kFollowLooks = 4096;  // looks of an idle following block, 1 to 2 us each
+constexpr int kFollowPerCu = 2;     // following blocks per CU
+
 // The pool's second stream, made to wait for what s holds so far; s itself
 // where the stream or its events cannot be had.
 hipStream_t fork_side(ssm_pool* p, hipStream_t s) {
@@ -1027,16 +1030,15 @@ ssm_status ssm_pool_prepare(ssm_pool* p, int32_t count, const int32_t* slots, in
     int2* dit = (int2*)(ws + o_it);
     std::vector<PoolGraph> hg(nq);
     std::vector<int2> hbi, hit;
+    std::vector<int> hf;
     std::vector<int4> hgi;
     for (int q = 0; q < nq; ++q) {
         Slot& sl = p->slots[ids[q]];
         bind(p, sl);
         hg[q] = sl.g;
-        for (int t = 0; t < sl.k; ++t) hbi.push_back(make_int2(q, t));
         for (int i0 = 0; i0 < sl.n; i0 += 256) hit.push_back(make_int2(q, i0));
     }
     hipError_t e = hipMemcpyAsync(dg, hg.data(), sizeof(PoolGraph) * nq, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(dbi, hbi.data(), sizeof(int2) * nbfs, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(dit, hit.data(), sizeof(int2) * nitems, hipMemcpyHostToDevice, s);
     // stage 1: CSR checks, selection and BFS
     if (e == hipSuccess) e = pool_prep_init(dg, nq, nmax, s);
@@ -1044,8 +1046,34 @@ ssm_status ssm_pool_prepare(ssm_pool* p, int32_t count, const int32_t* slots, in
         hipLaunchKernelGGL(k_pool_validate, dim3((int)nitems), dim3(256), 0, s, dg, dit);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = pool_select(dg, nq, nmax, s);
-    if (e == hipSuccess) e = pool_bfs(dg, dbi, (int)nbfs, dq, gq_stride, bfs_blocks, s);
+    // The BFS follow the selections on the second stream where that pays, from
+    // a record that takes the place of their items (3 + k ints per graph, k >=
+    // 3, where the items are 2 k).
+    hipStream_t aside = e == hipSuccess && pool_follows(nq) ? fork_side(p, s) : s;
+    if (aside != s) {
+        int* follow = (int*)dbi;
+        hf.assign(3 * (size_t)nq + nbfs, 0);
+        for (int q = 1; q < nq; ++q) hf[2 * nq + q] = hf[2 * nq + q - 1] + p->slots[ids[q - 1]].k;
+        std::fill(hf.begin() + 3 * nq, hf.end(), -1);
+        e = hipMemcpyAsync(follow, hf.data(), sizeof(int) * hf.size(), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = hipEventRecord(p->forked, s);
+        if (e == hipSuccess) e = hipStreamWaitEvent(aside, p->forked, 0);
+        if (e == hipSuccess) e = pool_select(dg, nq, nmax, follow, s);
+        // what is left when the selections and their followers are through
+        // runs after both
+        if (e == hipSuccess)
+            e = pool_bfs_follow(dg, nq, follow, kFollowLooks, dq, gq_stride,
+                                std::min(bfs_blocks, kFollowPerCu * num_cus()), aside);
+        const hipError_t j = join_side(p, s);
+        if (e == hipSuccess) e = j;
+        if (e == hipSuccess) e = pool_bfs_follow(dg, nq, follow, 0, dq, gq_stride, bfs_blocks, s);
+    } else if (e == hipSuccess) {
+        for (int q = 0; q < nq; ++q)
+            for (int t = 0; t < p->slots[ids[q]].k; ++t) hbi.push_back(make_int2(q, t));
+        e = hipMemcpyAsync(dbi, hbi.data(), sizeof(int2) * nbfs, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = pool_select(dg, nq, nmax, nullptr, s);
+        if (e == hipSuccess) e = pool_bfs(dg, dbi, (int)nbfs, dq, gq_stride, bfs_blocks, s);
+    }
     std::vector<int> hinfo(8 * (size_t)nq);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_pool_gather_info, dim3(div_up(8 * nq, 256)), dim3(256), 0, s, dg, nq, dinfo);

@@ -206,7 +206,13 @@ struct PoolGraph {
 // (graph, rank) items over a persistent grid with gq_stride ints of overflow
 // queue per block.
 hipError_t pool_prep_init(const PoolGraph* gs, int count, int nmax, hipStream_t s);
-hipError_t pool_select(const PoolGraph* gs, int count, int nmax, hipStream_t s);
+// follow (optional): where the selections publish their pivots for
+// pool_bfs_follow, which runs the BFS beside them: per graph a 0, a 0 and the
+// sum of k over the graphs before it, then per graph and rank a -1.
+bool pool_follows(int count);
+hipError_t pool_bfs_follow(const PoolGraph* gs, int count, int* follow, int looks, int* gq, long long gq_stride,
+                           int blocks, hipStream_t s);
+hipError_t pool_select(const PoolGraph* gs, int count, int nmax, int* follow, hipStream_t s);
 int pool_bfs_blocks(int nitems);
 hipError_t pool_bfs(const PoolGraph* gs, const int2* items, int nitems, int* gq, long long gq_stride, int blocks,
                     hipStream_t s);
