@@ -625,7 +625,7 @@ ssm_status kmeans_pivots(int32_t n, int32_t k, const int32_t* pivots, const int3
     // the matrix form's digits; other counts (distances above 32,639, sums
     // above 2^47) take the vector form, as does a forced km_chunk
     const int ly = km_digit_count(dmax), ls = std::max(2, km_digit_count((double)n * dmax));
-    const bool mx = ly <= 2 && ls <= 6 && variant("km_chunk") == 0;
+    bool mx = ly <= 2 && ls <= 6 && variant("km_chunk") == 0;
     const int nkb = div_up(k, 64) * 4, kc = div_up(k, 16) * 16;
     // launch shapes
     const int nb = div_up(n, kKmBlock);
@@ -652,24 +652,40 @@ ssm_status kmeans_pivots(int32_t n, int32_t k, const int32_t* pivots, const int3
     nbx = div_up(n, span);
     // workspace
     const size_t kk = (size_t)k * k, w = (size_t)(k + 1) * k;
-    size_t off = 0;
+    size_t off = 0, o_st, o_n, o_a, o_q, o_fb, o_tb, o_as, o_ch,
+           o_y, o_sq, o_part, o_s2, o_ps, o_pn, o_tk, o_nd;
     auto take = [&](size_t bytes) {
         const size_t o = off;
         off += (bytes + 255) & ~(size_t)255;
         return o;
     };
-    const size_t o_st = take(sizeof(double) * (kk + kKmPad)), o_n = take(sizeof(double) * k),
-                 o_a = take(sizeof(double) * k), o_q = take(sizeof(long long) * n),
-                 o_fb = take(mx ? 0 : sizeof(double) * (size_t)nchunks * n),
-                 o_tb = take(mx ? 0 : sizeof(int) * (size_t)nchunks * n),
-                 o_as = take(sizeof(int) * (size_t)n), o_ch = take(sizeof(int) * kKmCtl),
-                 o_y = take(mx ? sizeof(uint4) * (size_t)ly * nkb * n : 0),
-                 o_sq = take(mx ? sizeof(uint4) * (size_t)ls * nkb * kc : 0),
-                 o_part = take(sizeof(unsigned long long) * (size_t)nbx * w), o_s2 = take(sizeof(unsigned long long) * w),
-                 o_ps = take(sizeof(long long) * (size_t)nb * k), o_pn = take(sizeof(int) * (size_t)nb * k),
-                 o_tk = take((size_t)n), o_nd = take(sizeof(int) * k);
+    auto lay_out = [&] {
+        off = 0;
+        o_st = take(sizeof(double) * (kk + kKmPad));
+        o_n = take(sizeof(double) * k);
+        o_a = take(sizeof(double) * k);
+        o_q = take(sizeof(long long) * n);
+        o_fb = take(mx ? 0 : sizeof(double) * (size_t)nchunks * n);
+        o_tb = take(mx ? 0 : sizeof(int) * (size_t)nchunks * n);
+        o_as = take(sizeof(int) * (size_t)n);
+        o_ch = take(sizeof(int) * kKmCtl);
+        o_y = take(mx ? sizeof(uint4) * (size_t)ly * nkb * n : 0);
+        o_sq = take(mx ? sizeof(uint4) * (size_t)ls * nkb * kc : 0);
+        o_part = take(sizeof(unsigned long long) * (size_t)nbx * w);
+        o_s2 = take(sizeof(unsigned long long) * w);
+        o_ps = take(sizeof(long long) * (size_t)nb * k);
+        o_pn = take(sizeof(int) * (size_t)nb * k);
+        o_tk = take((size_t)n);
+        o_nd = take(sizeof(int) * k);
+    };
+    lay_out();
     char* ws = nullptr;
     ssm_status st = salloc((void**)&ws, off);
+    if (st == SSM_E_NOMEM && mx) {  // the matrix form also holds the table's digits
+        mx = false;
+        lay_out();
+        st = salloc((void**)&ws, off);
+    }
     if (st != SSM_OK) return st;
     double* ST = (double*)(ws + o_st);
     double* N = (double*)(ws + o_n);
