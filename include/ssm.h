@@ -417,7 +417,8 @@ void ssm_release_cache(void);
  *   sweep_blocks_per_cu N, sweep_waves 4|16 (waves per block),
  *   sweep_tune -1 (no timing of launch shapes: the rule shape; the FP32
  *   sweep otherwise times its shapes on the first loop of at least 24
- *   sweeps per graph shape and keeps the fastest),
+ *   sweeps per graph shape, on the loop's own sweeps where they suffice,
+ *   and keeps the fastest),
  *   sweep_perm -1|2 (caller's node order, always reorder),
  *   sweep_f64_terms -1 (FP64 sweeps of small graphs one thread per node
  *   instead of a lane group per node; same result), sweep_f64_hubs -1 (FP64

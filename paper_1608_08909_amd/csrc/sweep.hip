@@ -797,10 +797,18 @@ static SweepPlan plan_sweep(const ssm_terms* t, ssm_prec p) {
 // The FP32 sweep's result does not depend on its launch shape (split, block
 // shape, grid: see k_sweep_f32), so the first FP32 sweep loop of at least
 // kTuneMinIters sweeps on a graph shape times every candidate shape for a
-// few sweeps on scratch copies of the layout and keeps the fastest, per
-// device and (n, arcs, padded k, table extents, distance width, node
-// order).  Forced variants skip the tuning.
+// few sweeps and keeps the fastest, per device and (n, arcs, padded k, table
+// extents, distance width, node order).  Forced variants skip the tuning.
+//
+// The sweeps timed are the loop's own where it has enough of them and no stop
+// test: every shape gives the same bits, so only a slower shape's excess is
+// lost.  Else they run on scratch copies of the layout.  Shapes whose grid
+// comes out the same are timed once.  First loop on a graph, trials on copies
+// -> its own sweeps: 300 sweeps of a 1M-node preferential-attachment graph,
+// k = 200 (24 shapes), 59.0 -> 45.6 ms (41 once tuned); 100 of a 3.25M-node mesh,
+// k = 100 (6), 27.9 -> 22.0 ms (20.2 once tuned).
 constexpr int kTuneMinIters = 24;
+constexpr int kTuneReps = 3;  // sweeps timed per shape, after one to warm up
 
 struct PlanKey {
     int dev, n, nnz, kpad, W, L, dbytes, ordered, mode;
@@ -819,26 +827,36 @@ static bool sweep_shape_forced() {
            variant("sweep_mode") || variant("sweep_tune") == -1;
 }
 
-// Times `reps` sweeps of plan pl on scratch buffers ya, yb (ya holds a copy
-// of the layout); 0 on error.
-static float time_plan(const SweepPlan& pl, hipStream_t s, const ssm_csr* g, ssm_terms* t, float2* ya, float2* yb,
-                       hipEvent_t e0, hipEvent_t e1, int reps) {
+// Sets up a sweep loop from x: its stop words and, in FP32, the pivots'
+// coordinates.
+static void loop_init(const ssm_terms* t, ssm_prec p, const void* x, int iters, hipStream_t s) {
+    hipLaunchKernelGGL(k_stop_init, dim3(1), dim3(64), 0, s, t->stopw, iters);
+    if (p == SSM_FP32 && iters > 0)
+        hipLaunchKernelGGL(k_gather_pivots, dim3(div_up(t->kpad, 256)), dim3(256), 0, s, t->kpad, t->pivots,
+                           (const float2*)x, t->pc);
+}
+
+// Runs sweeps *done .. *done + kTuneReps of an FP32 loop with plan pl and times
+// all but the first; 0 on error (*done counts the sweeps run in any case).
+static float time_plan(const SweepPlan& pl, hipStream_t s, const ssm_csr* g, ssm_terms* t, void* const (&bufs)[2],
+                       int* done, hipEvent_t e0, hipEvent_t e1) {
     float2* pcb[2] = {t->pc, t->pc + t->kpad};
-    hipLaunchKernelGGL(k_stop_init, dim3(1), dim3(64), 0, s, t->stopw, 0);
-    hipLaunchKernelGGL(k_gather_pivots, dim3(div_up(t->kpad, 256)), dim3(256), 0, s, t->kpad, t->pivots,
-                       (const float2*)ya, pcb[0]);
-    sweep_once(pl, SSM_FP32, s, g, t, ya, yb, pcb[0], pcb[1]);  // warm
-    float2* buf[2] = {yb, ya};
-    if (hipEventRecord(e0, s) != hipSuccess) return 0.f;
-    for (int r = 0; r < reps; ++r)
-        sweep_once(pl, SSM_FP32, s, g, t, buf[r & 1], buf[(r + 1) & 1], pcb[(r + 1) & 1], pcb[r & 1]);
+    for (int r = 0; r <= kTuneReps; ++r, ++*done) {
+        const int cur = *done & 1;
+        if (r == 1 && hipEventRecord(e0, s) != hipSuccess) return 0.f;
+        sweep_once(pl, SSM_FP32, s, g, t, bufs[cur], bufs[cur ^ 1], pcb[cur], pcb[cur ^ 1]);
+    }
     if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) return 0.f;
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, e0, e1) != hipSuccess) return 0.f;
     return ms;
 }
 
-static SweepPlan tuned_plan(const ssm_csr* g, ssm_terms* t, const void* x, int iters, hipStream_t s) {
+// The tuned plan; *done = sweeps of the loop already run by the tuning (its
+// stop words and pivot coordinates are then set up).
+static SweepPlan tuned_plan(const ssm_csr* g, ssm_terms* t, void* const (&bufs)[2], int iters, double tol, int* done,
+                            hipStream_t s) {
+    *done = 0;
     SweepPlan rule = plan_sweep(t, SSM_FP32);
     if (iters < kTuneMinIters || sweep_shape_forced()) return rule;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -859,19 +877,28 @@ static SweepPlan tuned_plan(const ssm_csr* g, ssm_terms* t, const void* x, int i
             if (split > nwords) continue;
             for (int bpc : {1, 2, 3, 4, 6, 8}) {
                 if (waves == 16 && bpc > 2) continue;
-                cand.push_back(shape_f32(t, mode, tab, split, waves, bpc));
+                const SweepPlan pl = shape_f32(t, mode, tab, split, waves, bpc);
+                if (!cand.empty() && cand.back().block == pl.block && cand.back().split == pl.split &&
+                    cand.back().grid == pl.grid)
+                    continue;
+                cand.push_back(pl);
             }
         }
     }
+    const bool own = tol <= 0.0 && iters >= (int)cand.size() * (1 + kTuneReps);
     float2* y = nullptr;
-    if (salloc((void**)&y, sizeof(float2) * 2 * (size_t)t->n) != SSM_OK) return rule;
+    if (!own && salloc((void**)&y, sizeof(float2) * 2 * (size_t)t->n) != SSM_OK) return rule;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     SweepPlan best = rule;
     float best_ms = 0.f;
-    bool ok = hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess &&
-              hipMemcpyAsync(y, x, sizeof(float2) * (size_t)t->n, hipMemcpyDeviceToDevice, s) == hipSuccess;
+    bool ok = hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
+    if (ok && !own)
+        ok = hipMemcpyAsync(y, bufs[0], sizeof(float2) * (size_t)t->n, hipMemcpyDeviceToDevice, s) == hipSuccess;
+    void* const copies[2] = {y, y ? y + t->n : nullptr};
+    int spent = 0;  // sweeps run on the copies
+    if (ok) loop_init(t, SSM_FP32, own ? bufs[0] : y, iters, s);
     for (size_t c = 0; ok && c < cand.size(); ++c) {
-        const float ms = time_plan(cand[c], s, g, t, y, y + t->n, e0, e1, 3);
+        const float ms = time_plan(cand[c], s, g, t, own ? bufs : copies, own ? done : &spent, e0, e1);
         if (ms <= 0.f) {
             ok = false;
             break;
@@ -881,7 +908,7 @@ static SweepPlan tuned_plan(const ssm_csr* g, ssm_terms* t, const void* x, int i
             best = cand[c];
         }
     }
-    (void)hipStreamSynchronize(s);  // idle before the scratch is reused
+    if (!own) (void)hipStreamSynchronize(s);  // idle before the scratch is reused
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     sfree(y);
@@ -900,17 +927,15 @@ static SweepPlan tuned_plan(const ssm_csr* g, ssm_terms* t, const void* x, int i
 // asked for.
 static ssm_status sweep_loop(const ssm_csr* g, ssm_terms* t, ssm_prec p, void* const (&bufs)[2], int32_t iters,
                              double tol, int32_t* iters_done_host, hipStream_t s) {
-    const SweepPlan pl = p == SSM_FP32 ? tuned_plan(g, t, bufs[0], iters, s) : plan_sweep(t, p);
+    int from = 0;
+    const SweepPlan pl = p == SSM_FP32 ? tuned_plan(g, t, bufs, iters, tol, &from, s) : plan_sweep(t, p);
     const size_t xbytes = (p == SSM_FP64 ? sizeof(double) : sizeof(float)) * 2 * (size_t)t->n;
     void* const x = bufs[0];
     const int mblocks = std::min(div_up(t->n, 256), kStopBlocks);
     double* parts = t->red;
     float2* pcb[2] = {t->pc, t->pc + t->kpad};
-    hipLaunchKernelGGL(k_stop_init, dim3(1), dim3(64), 0, s, t->stopw, iters);
-    if (p == SSM_FP32 && iters > 0)
-        hipLaunchKernelGGL(k_gather_pivots, dim3(div_up(t->kpad, 256)), dim3(256), 0, s, t->kpad, t->pivots,
-                           (const float2*)x, pcb[0]);
-    for (int it = 0; it < iters; ++it) {
+    if (from == 0) loop_init(t, p, x, iters, s);
+    for (int it = from; it < iters; ++it) {
         const int cur = it & 1;
         sweep_once(pl, p, s, g, t, bufs[cur], bufs[cur ^ 1], pcb[cur], pcb[cur ^ 1]);
         if (tol > 0.0) {
