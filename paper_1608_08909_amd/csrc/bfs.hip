@@ -2422,7 +2422,9 @@ static ssm_status mssp_ring(const ssm_csr* g, int32_t k, const int32_t* pivots, 
     if (forced != 1 && (forced < 0 || sel_bits_fit(n) || variant("bfs_ell") || variant("bfs_grp") ||
                         variant("bfs_rowq") || variant("bfs_loads") || variant("bfs_lanes")))
         return SSM_OK;
-    if (Pages(n).count < 2 * kPagesSpare) return SSM_OK;
+    const int most = variant("bfs_pages");  // override: pages of the pool at most
+    const Pages pg(n, most > 0 ? most : 65535);
+    if (pg.count < 2 * kPagesSpare) return SSM_OK;
     const int W = ell_width(g, s);
     if (forced != 1 && W != 8) return SSM_OK;
     const int batch = (int)std::max<long long>(1, std::min<long long>(k, (1LL << 31) / (2LL * n)));
@@ -2438,7 +2440,7 @@ static ssm_status mssp_ring(const ssm_csr* g, int32_t k, const int32_t* pivots, 
         for (int b0 = 0; b0 < k && e == hipSuccess; b0 += batch) {
             auto kern = W == 8 ? k_bfs_ring<8> : W == 16 ? k_bfs_ring<16> : k_bfs_ring<32>;
             hipLaunchKernelGGL(kern, dim3(std::min(batch, k - b0)), dim3(kBfsBlock), 0, s, n, g->row_ptr, g->col_idx,
-                               ell, pivots + b0, dist + (size_t)b0 * n, gq, aux + b0, aux + k);
+                               ell, pivots + b0, dist + (size_t)b0 * n, gq, aux + b0, aux + k, pg);
             e = hipGetLastError();
         }
         if (e == hipSuccess)

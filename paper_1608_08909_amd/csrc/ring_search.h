@@ -27,12 +27,13 @@ constexpr int kPagesSpare = 512;     // pages kept free when a level starts
 
 struct Pages {
     int shift, tab, count;  // log2 ids per page, table words, pages in the pool
-    __host__ __device__ explicit Pages(int n) : shift(7) {
+    // `most` (tuning) takes fewer pages than fit.
+    __host__ explicit Pages(int n, int most = 65535) : shift(7) {
         while ((((long long)n >> shift) + 2) * 2 > 53248) ++shift;
         tab = ((n >> shift) + 2) / 2;
-        count = min_int((kPagedBytes / 4 - 2 - tab) >> (shift - 5), 65535);
+        count = std::min((kPagedBytes / 4 - 2 - tab) >> (shift - 5), most);
     }
-    static __host__ __device__ int min_int(int a, int b) { return a < b ? a : b; }
+    __device__ Pages() : shift(5), tab(0), count(0) {}  // for the searches without pages
     __device__ __forceinline__ unsigned* pool(unsigned* set) const { return set + 2 + tab; }
     __device__ __forceinline__ unsigned short* table(unsigned* set) const { return (unsigned short*)(set + 2); }
     // Clears everything (call with the whole workgroup, barriers around).
@@ -120,7 +121,7 @@ __device__ __forceinline__ void put(const RingFrontier& f, int slot, int u) {
 // and m lies above dv.  m is only read: it changes between the rounds.
 template <int STATE, int N>
 __device__ __forceinline__ void ring_claim(const int (&u)[N], bool (&ok)[N], int n, unsigned* bits, const int* m,
-                                            int dv) {
+                                            int dv, const Pages& pg) {
     if (STATE == kRsBytes) {
         unsigned char* m8 = (unsigned char*)bits;
         unsigned old[N];
@@ -142,7 +143,6 @@ __device__ __forceinline__ void ring_claim(const int (&u)[N], bool (&ok)[N], int
             }
         }
     } else if (STATE == kRsPaged) {
-        const Pages pg(n);
         unsigned e[N];
 #pragma unroll
         for (int j = 0; j < N; ++j) {  // the entries in flight together
@@ -190,12 +190,12 @@ __device__ __forceinline__ void ring_claim(const int (&u)[N], bool (&ok)[N], int
 template <int W, int STATE>
 __device__ __forceinline__ int ring_wave_levels(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                  const int* __restrict__ ell, unsigned* bits, const int* m, int* q,
-                                                 RingFrontier& f, int len, int d0, int* ls, int& nl) {
+                                                 RingFrontier& f, int len, int d0, int* ls, int& nl, const Pages& pg) {
     constexpr int G = W / 4;
     const int lane = lane_id(), sub = lane % G;
     while (len > 0 && len <= wave_level_nodes<W>() && (STATE != kRsBytes || d0 + nl + 1 < kM7Sat) &&
            nl < kRingLevels && f.next <= f.cap / 2 &&
-           (STATE != kRsPaged || (int)bits[0] <= Pages(n).count - kPagesSpare)) {
+           (STATE != kRsPaged || (int)bits[0] <= pg.count - kPagesSpare)) {
         const int at = f.at + lane / G;  // below cap: the frontier ends at f.next
         const int v = lane / G < len ? q[at] : -1;
         int4 nb = make_int4(-1, -1, -1, -1);
@@ -204,7 +204,7 @@ __device__ __forceinline__ int ring_wave_levels(int n, const int* __restrict__ r
         int cnt = 0;
         const int u[4] = {nb.x, nb.y, nb.z, nb.w};
         bool ok[4];
-        ring_claim<STATE>(u, ok, n, bits, m, dv);
+        ring_claim<STATE>(u, ok, n, bits, m, dv, pg);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint64_t mk = __ballot(ok[j]);
@@ -220,7 +220,7 @@ __device__ __forceinline__ int ring_wave_levels(int n, const int* __restrict__ r
             for (int e = rp[h] + W - 1 + lane; __any(e < e1); e += kWave) {
                 const int t[1] = {e < e1 ? ci[e] : -1};
                 bool okt[1];
-                ring_claim<STATE>(t, okt, n, bits, m, dv);
+                ring_claim<STATE>(t, okt, n, bits, m, dv, pg);
                 const uint64_t mk = __ballot(okt[0]);
                 if (okt[0]) put(f, cnt + mask_rank(mk), t[0]);
                 cnt += __popcll(mk);
@@ -241,17 +241,17 @@ __device__ __forceinline__ int ring_wave_levels(int n, const int* __restrict__ r
 // q: the LDS queue of cap entries, lheavy: the long-row list, bits: the
 // visited set (state bytes: flags clear on entry and on return).  gq holds
 // 2 n ints (queue overflow, long rows).  Returns the number of nodes found, or
-// -1 as soon as a frontier is wider than `widest` or the pages ran out;
-// *depth (thread 0): the largest distance.  Ends past a barrier.
+// -1 as soon as a frontier is wider than `widest`, the pages ran out or more
+// than n nodes were found; *depth (thread 0): the largest distance.  Ends past
+// a barrier.
 template <int W, int STATE, class Sink>
 __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                             const int* __restrict__ ell, int src, int* q, int cap, int* lheavy,
                                             unsigned* bits, const int* m, Sink sink, int* gq, int widest = INT_MAX,
-                                            int* depth = nullptr) {
+                                            int* depth = nullptr, Pages pg = Pages()) {
     __shared__ int2 s_slot[3];
     __shared__ int s_wave[4];
     __shared__ int s_ls[kRingLevels + 2];  // queue positions where the levels since the last flush start
-    const Pages pg(n);
     if (STATE == kRsPaged)
         pg.clear(bits);
     else if (STATE != kRsBytes)
@@ -287,7 +287,7 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
             if (threadIdx.x < kWave) {
                 RingFrontier g = f;
                 int l = nl;
-                const int left = ring_wave_levels<W, STATE>(n, rp, ci, ell, bits, m, q, g, len, d0, s_ls, l);
+                const int left = ring_wave_levels<W, STATE>(n, rp, ci, ell, bits, m, q, g, len, d0, s_ls, l, pg);
                 if (threadIdx.x == 0) {
                     s_wave[0] = left;
                     s_wave[1] = l;
@@ -307,7 +307,7 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
             f.lcur = q + f.at;
             f.gcur = gq + (lds > 0 ? 0 : f.at - cap);
             len = ell_level_auto<W>(n, rp, ci, ell, len, f, [&](const auto& u, auto& ok) {
-                ring_claim<STATE>(u, ok, n, bits, m, dv);
+                ring_claim<STATE>(u, ok, n, bits, m, dv, pg);
             });
             ++nl;
             f.at = f.next;
@@ -316,6 +316,10 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
         }
         total += f.next - before;
         if (len > widest) return -1;  // uniform
+        // Paged bits forget the levels before the last, which no arc leads back
+        // to in a symmetric graph.  In one that is not (the caller's error) a
+        // node can be found again, for ever on a one-way cycle.
+        if (STATE == kRsPaged && total > n) return -1;  // uniform
         bool full = false;
         if (STATE == kRsPaged) {
             const bool over = bits[1] != 0;
@@ -372,12 +376,13 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
 }
 
 // Block b: BFS from pivots[b] into dist[b][*] on one workgroup (gq: 2 n ints
-// per block).  reached[b] = nodes found, or -1 (the pages ran out: the row is
-// incomplete); *ecc_max = largest eccentricity seen.
+// per block).  reached[b] = nodes found, or -1 (the pages ran out, or the graph
+// is not symmetric: the row is incomplete); *ecc_max = largest eccentricity
+// seen.
 template <int W>
 __global__ __launch_bounds__(kBfsBlock) void k_bfs_ring(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                         const int* __restrict__ ell, const int* __restrict__ pivots,
-                                                        int* dist, int* gq, int* reached, int* ecc_max) {
+                                                        int* dist, int* gq, int* reached, int* ecc_max, Pages pg) {
     __shared__ __align__(16) unsigned char pool[kRingPool];
     __shared__ int s_depth;
     int* lheavy = (int*)pool;
@@ -386,7 +391,7 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_ring(int n, const int* __rest
     const int b = blockIdx.x;
     const int found = ring_search<W, kRsPaged>(n, rp, ci, ell, pivots[b], q, (kRingPool - 4 * kHeavyCap - kPagedBytes) / 4,
                                             lheavy, bits, nullptr, PlainRowSink{dist + (size_t)b * n},
-                                            gq + (size_t)b * 2 * n, INT_MAX, &s_depth);
+                                            gq + (size_t)b * 2 * n, INT_MAX, &s_depth, pg);
     if (threadIdx.x == 0) {
         reached[b] = found;
         if (found > 0) atomicMax(ecc_max, s_depth);
