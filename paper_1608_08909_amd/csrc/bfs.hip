@@ -1019,7 +1019,7 @@ static void launch_bfs_wg(int blocks, hipStream_t s, int n, const int* rp, const
 constexpr int kBfsGrp = 2;
 hipError_t launch_bfs_grp(int vw, int rows, hipStream_t s, int n, const int* rp, const int* ci, const int* pivots,
                           int* dist, int2* queues, int* ctl, unsigned long long* bars, int* reached, int* ecc,
-                          int* status);
+                          int* status, const int* from);
 int bfs_grp_fits(int rows);
 static ssm_status mssp_ring(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dist, int32_t* dmax_out_host,
                             bool* done, hipStream_t s);
@@ -1205,7 +1205,7 @@ ssm_status mssp(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dis
             e = hipMemsetAsync(gbars, 0, sizeof(unsigned long long) * (size_t)batch * 16 + 256, s);
             if (e == hipSuccess)
                 e = launch_bfs_grp(vw, nb, s, n, g->row_ptr, g->col_idx, pivots + b0, D, queues, gctl, gbars, reached,
-                                   ecc, gstatus);
+                                   ecc, gstatus, nullptr);
             if (e == hipSuccess) e = hipMemcpyAsync(&hstatus, gstatus, sizeof(int), hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             if (e == hipSuccess && hstatus) break;
@@ -1529,7 +1529,9 @@ __device__ __forceinline__ void append4_agent(const int (&u)[4], const bool (&ok
 // agent-scope compare-and-swap on the distance, one reservation per wave on
 // the row's frontier counter (ctl + 32 g: three level slots) and a barrier
 // of the row's blocks per level (bars + 16 g).  A barrier that never fills
-// sets status[0] and both blocks leave.
+// sets status[0] and both blocks leave.  With `from`, row g is taken up at level
+// from[g] (-1: it is complete): dist holds the levels up to it, the queue and
+// its counter that level's nodes (k_bfs_front), reached[g] the nodes found.
 
 __device__ __forceinline__ int2 load_agent_int2(const int2* p) {
     const unsigned long long v =
@@ -1545,7 +1547,7 @@ template <int VW>
 __global__ __launch_bounds__(kBfsBlock) void k_bfs_grp(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                        const int* __restrict__ pivots, int* dist, int2* queues,
                                                        int* ctl, unsigned long long* bars, int* reached,
-                                                       int* ecc_max, int* status) {
+                                                       int* ecc_max, int* status, const int* __restrict__ from) {
     const int g = blockIdx.x / kBfsGrp, part = blockIdx.x % kBfsGrp;
     int* D = dist + (size_t)g * n;
     int2* cur = queues + (size_t)g * 2 * n;
@@ -1554,9 +1556,10 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_grp(int n, const int* __restr
     unsigned long long* bar = bars + 16 * g;
     __shared__ int s_found;
     unsigned long long epoch = 0;
-    const int src = pivots[g];
+    const int src = pivots[g], start = from ? from[g] : 0;
+    if (start < 0) return;  // both blocks
     if (threadIdx.x == 0) s_found = 0;
-    if (part == 0 && threadIdx.x == 0) {
+    if (!from && part == 0 && threadIdx.x == 0) {
         store_agent(&D[src], 0);
         store_agent_int2(&cur[0], make_int2(rp[src], rp[src + 1]));
         store_agent(&c[0], 1);
@@ -1569,7 +1572,7 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_grp(int n, const int* __restr
     }
     const int sub = threadIdx.x % VW, grp = threadIdx.x / VW, ngrp = blockDim.x / VW;
     const int gg = part * ngrp + grp, ngg = kBfsGrp * ngrp;  // this lane group among the row's groups
-    int level = 0;
+    int level = start;
     for (;;) {
         const int len = min(load_agent(&c[level % 3]), n);
         if (len == 0) break;
@@ -1641,7 +1644,7 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_grp(int n, const int* __restr
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        atomicAdd(&reached[g], s_found + (part == 0 ? 1 : 0));
+        atomicAdd(&reached[g], s_found + (part == 0 && !from ? 1 : 0));
         if (part == 0) atomicMax(ecc_max, level - 1);
     }
 }
@@ -1649,21 +1652,21 @@ __global__ __launch_bounds__(kBfsBlock) void k_bfs_grp(int n, const int* __restr
 template <int VW>
 static hipError_t launch_bfs_grp_w(int rows, hipStream_t s, int n, const int* rp, const int* ci, const int* pivots,
                                    int* dist, int2* queues, int* ctl, unsigned long long* bars, int* reached,
-                                   int* ecc, int* status) {
-    void* args[] = {&n, &rp, &ci, &pivots, &dist, &queues, &ctl, &bars, &reached, &ecc, &status};
+                                   int* ecc, int* status, const int* from) {
+    void* args[] = {&n, &rp, &ci, &pivots, &dist, &queues, &ctl, &bars, &reached, &ecc, &status, &from};
     return hipLaunchCooperativeKernel((const void*)k_bfs_grp<VW>, dim3(rows * kBfsGrp), dim3(kBfsBlock), args, 0, s);
 }
 
 hipError_t launch_bfs_grp(int vw, int rows, hipStream_t s, int n, const int* rp, const int* ci, const int* pivots,
                           int* dist, int2* queues, int* ctl, unsigned long long* bars, int* reached, int* ecc,
-                          int* status) {
+                          int* status, const int* from) {
     switch (vw) {
-        case 2: return launch_bfs_grp_w<2>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status);
-        case 4: return launch_bfs_grp_w<4>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status);
-        case 8: return launch_bfs_grp_w<8>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status);
-        case 16: return launch_bfs_grp_w<16>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status);
-        case 32: return launch_bfs_grp_w<32>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status);
-        default: return launch_bfs_grp_w<64>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status);
+        case 2: return launch_bfs_grp_w<2>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status, from);
+        case 4: return launch_bfs_grp_w<4>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status, from);
+        case 8: return launch_bfs_grp_w<8>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status, from);
+        case 16: return launch_bfs_grp_w<16>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status, from);
+        case 32: return launch_bfs_grp_w<32>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status, from);
+        default: return launch_bfs_grp_w<64>(rows, s, n, rp, ci, pivots, dist, queues, ctl, bars, reached, ecc, status, from);
     }
 }
 
@@ -1673,6 +1676,79 @@ int bfs_grp_fits(int rows) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, (const void*)k_bfs_grp<8>, kBfsBlock, 0) != hipSuccess)
         return 0;
     return (long long)rows * kBfsGrp <= (long long)a * num_cus();
+}
+
+// Row blockIdx.y of those left at level from[row] (-1: complete): that level's
+// nodes as k_bfs_grp's frontier, their row bounds in the queue (any order) and
+// their number in the counter of the level (0 on entry).
+__global__ __launch_bounds__(256) void k_bfs_front(int n, const int* __restrict__ rp, const int* __restrict__ dist,
+                                                   const int* __restrict__ from, int2* queues, int* ctl) {
+    const int row = blockIdx.y, level = from[row];
+    if (level < 0) return;
+    const int* D = dist + (size_t)row * n;
+    int2* q = queues + (size_t)row * 2 * n;
+    int* count = ctl + 32 * row + level % 3;
+    for (int base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {  // uniform
+        const int i = base + threadIdx.x;
+        const bool at = i < n && D[i] == level;
+        const uint64_t mk = __ballot(at);
+        if (mk == 0) continue;
+        int slot = 0;
+        if (lane_id() == 0) slot = atomicAdd(count, (int)__popcll(mk));
+        slot = __builtin_amdgcn_readfirstlane(slot);
+        if (at) q[slot + mask_rank(mk)] = make_int2(rp[i], rp[i + 1]);
+    }
+}
+
+// The rows that k_bfs_ring left (host_from[t] >= 0), taken up by k_bfs_grp in
+// chunks of as many rows as are resident.  *done stays false, with reached and
+// dist no longer of use, where the workspace of one row cannot be had.
+static ssm_status rows_resume(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dist, int* reached, int* ecc,
+                              const int* from, const int* host_from, bool* done, hipStream_t s) {
+    const int n = g->n;
+    int chunk = (int)std::max<long long>(1, std::min<long long>({k, num_cus() / kBfsGrp, (1LL << 31) / (2LL * n)}));
+    while (chunk > 0 && !bfs_grp_fits(chunk)) chunk /= 2;
+    int2* queues = nullptr;
+    int* gctl = nullptr;  // as in mssp: frontier counters, barriers, status
+    ssm_status st = SSM_E_NOMEM;
+    while (chunk > 0 && st == SSM_E_NOMEM) {
+        st = salloc((void**)&queues, sizeof(int2) * 2 * (size_t)n * chunk);
+        if (st == SSM_E_NOMEM) chunk /= 2;
+    }
+    const size_t bars_at = sizeof(int) * 32 * (size_t)chunk,
+                 gctl_b = bars_at + sizeof(unsigned long long) * 16 * (size_t)chunk + 256;
+    if (st == SSM_OK) st = salloc((void**)&gctl, gctl_b);
+    if (st != SSM_OK) {
+        sfree(queues);
+        return st == SSM_E_NOMEM ? SSM_OK : st;
+    }
+    unsigned long long* bars = (unsigned long long*)((char*)gctl + bars_at);
+    int* status = (int*)(bars + 16 * (size_t)chunk);
+    const int vw = virtual_warp(g);
+    hipError_t e = hipSuccess;
+    int hstatus = 0;
+    for (int b0 = 0; b0 < k && e == hipSuccess && !hstatus; b0 += chunk) {
+        const int nb = std::min(chunk, k - b0);
+        if (std::all_of(host_from + b0, host_from + b0 + nb, [](int l) { return l < 0; })) continue;
+        int32_t* D = dist + (size_t)b0 * n;
+        e = hipMemsetAsync(gctl, 0, gctl_b, s);
+        if (e != hipSuccess) break;
+        hipLaunchKernelGGL(k_bfs_front, dim3(std::min(div_up(n, 256), 512), nb), dim3(256), 0, s, n, g->row_ptr, D,
+                           from + b0, queues, gctl);
+        e = hipGetLastError();
+        if (e == hipSuccess)
+            e = launch_bfs_grp(vw, nb, s, n, g->row_ptr, g->col_idx, pivots + b0, D, queues, gctl, bars, reached + b0,
+                               ecc, status, from + b0);
+        if (e == hipSuccess) e = hipMemcpyAsync(&hstatus, status, sizeof(int), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+    }
+    (void)hipStreamSynchronize(s);  // idle before the scratch is reused (also after an error)
+    sfree(queues);
+    sfree(gctl);
+    if (e != hipSuccess) return hip_fail(e, "multi-source BFS");
+    if (hstatus) return fail(SSM_E_DEVICE, "multi-source BFS: a row's barrier did not fill and was aborted");
+    *done = true;
+    return SSM_OK;
 }
 
 // Pivots t0 .. t1-1 of max/min sampling in one cooperative launch, over the
@@ -2410,12 +2486,12 @@ static hipError_t launch_select_ell(int W, bool m8, hipStream_t s, int n, const 
 
 namespace ssm {
 
-// The k rows by k_bfs_ring.  *done stays false where the form does not apply,
-// its workspace cannot be had or a row ran out of pages; the forms of mssp then
-// run.  By default for graphs whose visited bits do not fit in LDS and whose
-// rows have at most 8 entries: 100 rows of a 3.25M-node mesh 37.3 -> 29.5 ms (37.7
-// with 16 slots per padded row, so not above).  (tuning: bfs_ring -1 = never,
-// 1 = any graph)
+// The k rows by k_bfs_ring; those it leaves are taken up by k_bfs_grp at the
+// level they reached (rows_resume).  *done stays false where the form does not
+// apply or its workspace cannot be had; the forms of mssp then run.  By default
+// for graphs whose visited bits do not fit in LDS and whose rows have at most 8
+// entries: 100 rows of a 3.25M-node mesh 37.3 -> 29.5 ms (37.7 with 16 slots per
+// padded row, so not above).  (tuning: bfs_ring -1 = never, 1 = any graph)
 static ssm_status mssp_ring(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dist, int32_t* dmax_out_host,
                             bool* done, hipStream_t s) {
     const int n = g->n, forced = variant("bfs_ring");
@@ -2428,36 +2504,46 @@ static ssm_status mssp_ring(const ssm_csr* g, int32_t k, const int32_t* pivots, 
     const int W = ell_width(g, s);
     if (forced != 1 && W != 8) return SSM_OK;
     const int batch = (int)std::max<long long>(1, std::min<long long>(k, (1LL << 31) / (2LL * n)));
-    int *ell = nullptr, *gq = nullptr, *aux = nullptr;  // aux: reached[k], ecc
+    int *ell = nullptr, *gq = nullptr, *aux = nullptr;  // aux: reached[k], from[k], ecc, stop
+    const size_t aux_b = sizeof(int) * (2 * (size_t)k + 2);
     ssm_status st = salloc((void**)&ell, sizeof(int) * (size_t)n * W);
     if (st == SSM_OK) st = salloc((void**)&gq, sizeof(int) * 2 * (size_t)n * batch);
-    if (st == SSM_OK) st = salloc((void**)&aux, sizeof(int) * ((size_t)k + 1));
+    if (st == SSM_OK) st = salloc((void**)&aux, aux_b);
     hipError_t e = hipSuccess;
-    std::vector<int> host((size_t)k + 1);
+    std::vector<int> host(2 * (size_t)k + 2);
+    int *reached = aux, *from = aux + k, *ecc = aux + 2 * (size_t)k;
     if (st == SSM_OK) {
-        e = hipMemsetAsync(aux, 0, sizeof(int) * ((size_t)k + 1), s);
+        e = hipMemsetAsync(aux, 0, aux_b, s);
+        // unfound nodes tell where a row that is left goes on
+        if (e == hipSuccess) e = hipMemsetAsync(dist, 0xff, sizeof(int) * (size_t)k * n, s);
         if (e == hipSuccess) e = ell_build(g, W, ell, s);
         for (int b0 = 0; b0 < k && e == hipSuccess; b0 += batch) {
             auto kern = W == 8 ? k_bfs_ring<8> : W == 16 ? k_bfs_ring<16> : k_bfs_ring<32>;
             hipLaunchKernelGGL(kern, dim3(std::min(batch, k - b0)), dim3(kBfsBlock), 0, s, n, g->row_ptr, g->col_idx,
-                               ell, pivots + b0, dist + (size_t)b0 * n, gq, aux + b0, aux + k, pg);
+                               ell, pivots + b0, dist + (size_t)b0 * n, gq, reached + b0, from + b0, ecc, ecc + 1, pg);
             e = hipGetLastError();
         }
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(host.data(), aux, sizeof(int) * ((size_t)k + 1), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(host.data(), aux, aux_b, hipMemcpyDeviceToHost, s);
         (void)hipStreamSynchronize(s);  // idle before the scratch is reused
     }
     sfree(ell);
     sfree(gq);
+    const auto symmetric = [&] { return std::none_of(host.begin(), host.begin() + k, [](int r) { return r < 0; }); };
+    bool whole = true;
+    if (st == SSM_OK && e == hipSuccess && symmetric() && host[2 * (size_t)k + 1]) {
+        whole = false;
+        st = rows_resume(g, k, pivots, dist, reached, ecc, from, host.data() + k, &whole, s);
+        if (st == SSM_OK && whole) e = hipMemcpyAsync(host.data(), aux, aux_b, hipMemcpyDeviceToHost, s);
+        (void)hipStreamSynchronize(s);
+    }
     sfree(aux);
     if (st == SSM_E_NOMEM && forced == 0) return SSM_OK;
     if (st != SSM_OK) return st;
     if (e != hipSuccess) return hip_fail(e, "multi-source BFS");
-    for (int t = 0; t < k; ++t)
-        if (host[t] < 0) return SSM_OK;
+    if (!whole || !symmetric()) return SSM_OK;
     for (int t = 0; t < k; ++t)
         if (host[t] != n) return fail(SSM_E_DISCONNECTED, "graph is not connected (a BFS missed nodes)");
-    *dmax_out_host = host[k];
+    *dmax_out_host = host[2 * (size_t)k];
     *done = true;
     return SSM_OK;
 }

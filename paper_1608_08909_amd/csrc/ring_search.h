@@ -19,9 +19,11 @@ enum RingState { kRsBytes = 0, kRsBits = 1, kRsFull = 2, kRsStamps = 3, kRsPaged
 // nodes lie in need bits.  A table of 16-bit entries names each page's bits in
 // a pool (0: none yet).  When the pool runs short, all of it is cleared and
 // the last two levels are put back.  A 3.25M-node mesh numbered by rows has up
-// to 4,000 pages of 128 ids in use and gains about 30 per level.  Numberings
-// that spread a level over more pages than the pool holds end the search
-// (kPages' second counter), and another form computes the rows.
+// to 4,000 pages of 128 ids in use and gains about 30 per level.  A search whose
+// last two levels alone fill the pool (wide levels, or a numbering that spreads
+// them) or whose next level finds it empty (the pool's second counter) is left
+// at its last complete level, the others of the launch soon after, and k_bfs_grp
+// takes the rows up from there.
 constexpr int kPagedBytes = 133120;  // table, pool and two counters: pages taken, pages refused
 constexpr int kPagesSpare = 512;     // pages kept free when a level starts
 
@@ -93,6 +95,8 @@ struct PlainRowSink {
 // as a level: stored at discovery, the list cost 14 us per pivot on a
 // 100k-node geometric graph.
 constexpr int kRingLevels = 128;  // levels between flushes at most
+constexpr int kRingStopLooks = 16;  // flushes between looks at the other searches' call to stop
+constexpr int kRingLeft = -2;       // ring_search: left at a complete level, to be taken up from there
 constexpr int kRingPool = 155648;  // LDS of a search: long rows, visited set, queue
 
 struct RingFrontier : Frontier {
@@ -240,15 +244,16 @@ __device__ __forceinline__ int ring_wave_levels(int n, const int* __restrict__ r
 // (kRsFull: all of them); every node found goes to the sink with its distance.
 // q: the LDS queue of cap entries, lheavy: the long-row list, bits: the
 // visited set (state bytes: flags clear on entry and on return).  gq holds
-// 2 n ints (queue overflow, long rows).  Returns the number of nodes found, or
-// -1 as soon as a frontier is wider than `widest`, the pages ran out or more
-// than n nodes were found; *depth (thread 0): the largest distance.  Ends past
-// a barrier.
+// 2 n ints (queue overflow, long rows).  Returns the number of nodes found, -1
+// as soon as a frontier is wider than `widest` or more than n nodes were found,
+// or kRingLeft where the pages ran out, which sets *stop, or *stop was set.
+// *end (thread 0): the largest distance (left: the last complete level, all of
+// it at the sink as well) and the nodes found.  Ends past a barrier.
 template <int W, int STATE, class Sink>
 __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                             const int* __restrict__ ell, int src, int* q, int cap, int* lheavy,
                                             unsigned* bits, const int* m, Sink sink, int* gq, int widest = INT_MAX,
-                                            int* depth = nullptr, Pages pg = Pages()) {
+                                            int2* end = nullptr, Pages pg = Pages(), int* stop = nullptr) {
     __shared__ int2 s_slot[3];
     __shared__ int s_wave[4];
     __shared__ int s_ls[kRingLevels + 2];  // queue positions where the levels since the last flush start
@@ -281,6 +286,7 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
     int total = 1, len = 1;       // nodes found; size of the current frontier
     int base = 0, d0 = 0, nl = 0;  // flushed: nodes, levels; complete levels since
     int step = 0;                  // block levels run: their counters rotate
+    int flushes = 0;
     while (len > 0) {
         const int before = f.next;
         if (len <= wave_level_nodes<W>() && (STATE != kRsBytes || d0 + nl + 1 < kM7Sat) && f.next <= cap / 2) {
@@ -320,16 +326,16 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
         // to in a symmetric graph.  In one that is not (the caller's error) a
         // node can be found again, for ever on a one-way cycle.
         if (STATE == kRsPaged && total > n) return -1;  // uniform
-        bool full = false;
+        bool full = false, over = false;
         if (STATE == kRsPaged) {
-            const bool over = bits[1] != 0;
+            over = bits[1] != 0;  // the level just run lacks nodes; over implies full
             full = (int)bits[0] > pg.count - kPagesSpare;
             __syncthreads();  // both read before the next level takes pages
-            if (over) return -1;  // uniform
         }
         if (len == 0 || nl >= kRingLevels || f.next > cap / 2 || full) {  // flush the complete levels (uniform)
             __syncthreads();
-            if (STATE == kRsPaged && full && len > 0) {  // the last complete level and the current frontier stay marked
+            bool leave = over;  // uniform
+            if (STATE == kRsPaged && !over && full && len > 0) {  // the last complete level and the current frontier stay marked
                 pg.clear(bits);
                 __syncthreads();
                 for (int pos = s_ls[nl - 1] + (int)threadIdx.x; pos < f.next; pos += blockDim.x) {
@@ -337,11 +343,26 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
                     pg.mark(bits, u, pg.table(bits)[u >> pg.shift]);
                 }
                 __syncthreads();
-                if ((int)bits[0] > pg.count - kPagesSpare) return -1;  // uniform: two levels alone fill the pool
+                leave = (int)bits[0] > pg.count - kPagesSpare;  // two levels alone fill the pool
+            }
+            if (STATE == kRsPaged && leave) {
+                if (threadIdx.x == 0) store_agent(stop, 1);
+            } else if (STATE == kRsPaged && len > 0 && ++flushes % kRingStopLooks == 0) {
+                if (threadIdx.x == 0) s_wave[0] = load_agent(stop);
+                __syncthreads();
+                leave = s_wave[0] != 0;
             }
             for (int l = threadIdx.x / kWave; l < nl; l += blockDim.x / kWave)
                 for (int pos = s_ls[l] + lane_id(); pos < s_ls[l + 1]; pos += kWave)
                     sink.put(base + pos, ring_get(f, q, pos), d0 + l);
+            if (STATE == kRsPaged && leave) {  // uniform
+                if (!over)
+                    for (int pos = f.at + (int)threadIdx.x; pos < f.next; pos += blockDim.x)
+                        sink.put(base + pos, ring_get(f, q, pos), d0 + nl);
+                if (threadIdx.x == 0) *end = over ? make_int2(d0 + nl - 1, total - len) : make_int2(d0 + nl, total);
+                __syncthreads();
+                return kRingLeft;
+            }
             base += f.at;
             d0 += nl;
             nl = 0;
@@ -359,7 +380,7 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
             __syncthreads();
         }
     }
-    if (depth && threadIdx.x == 0) *depth = d0 - 1;
+    if (end && threadIdx.x == 0) *end = make_int2(d0 - 1, total);
     if (STATE == kRsBytes) {
         uint4* w16 = (uint4*)bits;
         for (int w = threadIdx.x; w < (n + 15) / 16; w += blockDim.x) {
@@ -375,26 +396,28 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
     return total;
 }
 
-// Block b: BFS from pivots[b] into dist[b][*] on one workgroup (gq: 2 n ints
-// per block).  reached[b] = nodes found, or -1 (the pages ran out, or the graph
-// is not symmetric: the row is incomplete); *ecc_max = largest eccentricity
-// seen.
+// Block b: BFS from pivots[b] into dist[b][*] (pre-set to -1) on one workgroup
+// (gq: 2 n ints per block).  reached[b] = nodes found, or -1 (the graph is not
+// symmetric); from[b] = -1, or the level at which the search was left; *ecc_max
+// = largest eccentricity of the complete rows; *stop: 0 on entry.
 template <int W>
 __global__ __launch_bounds__(kBfsBlock) void k_bfs_ring(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                         const int* __restrict__ ell, const int* __restrict__ pivots,
-                                                        int* dist, int* gq, int* reached, int* ecc_max, Pages pg) {
+                                                        int* dist, int* gq, int* reached, int* from, int* ecc_max,
+                                                        int* stop, Pages pg) {
     __shared__ __align__(16) unsigned char pool[kRingPool];
-    __shared__ int s_depth;
+    __shared__ int2 s_end;
     int* lheavy = (int*)pool;
     unsigned* bits = (unsigned*)(lheavy + kHeavyCap);
     int* q = (int*)((unsigned char*)bits + kPagedBytes);
     const int b = blockIdx.x;
     const int found = ring_search<W, kRsPaged>(n, rp, ci, ell, pivots[b], q, (kRingPool - 4 * kHeavyCap - kPagedBytes) / 4,
                                             lheavy, bits, nullptr, PlainRowSink{dist + (size_t)b * n},
-                                            gq + (size_t)b * 2 * n, INT_MAX, &s_depth, pg);
+                                            gq + (size_t)b * 2 * n, INT_MAX, &s_end, pg, stop);
     if (threadIdx.x == 0) {
-        reached[b] = found;
-        if (found > 0) atomicMax(ecc_max, s_depth);
+        reached[b] = found == kRingLeft ? s_end.y : found;
+        from[b] = found == kRingLeft ? s_end.x : -1;
+        if (found > 0) atomicMax(ecc_max, s_end.x);
     }
 }
 

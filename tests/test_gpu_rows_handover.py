@@ -13,6 +13,42 @@ if torch.cuda.is_available():
     from paper_1608_08909_amd import ssm
 
 
+def _shuffled(g, seed):
+    p = np.random.Generator(np.random.PCG64(seed)).permutation(g.n)
+    return G.csr_from_edges(g.n, p[g.edges()], g.name + "-shuffled")
+
+
+def _check(g, piv):
+    print("case", g.name, g.n, len(piv), flush=True)
+    piv = np.asarray(piv, dtype=np.int32)
+    dist, delta, _ = ssm.bfs_pivots(ssm.DeviceGraph.from_csr(g), torch.from_numpy(piv).cuda())
+    ref = oracle.bfs_pivots(g.n, g.row_ptr, g.col_idx, piv)
+    assert np.array_equal(dist.cpu().numpy(), ref)
+    assert np.array_equal(delta.cpu().numpy(), ref.min(0))
+
+
+LATTICE = G.tri_grid(560, 555)
+LEFT = [(LATTICE, 3), (LATTICE, 140), (_shuffled(G.tri_grid(400, 410), 1), 3), (G.tree_plus(200000, 4), 3),
+        (G.star(150000), 3)]
+
+
+@pytest.mark.parametrize("g,k", LEFT, ids=[f"{g.name}-{k}" for g, k in LEFT])
+def test_rows_taken_up(g, k, forced):
+    """Rows from the middle run out of pages, rows from the corners are called off:
+    both are taken up at the level they reached (140 rows: in two chunks)."""
+    forced("bfs_ring", 1)
+    forced("bfs_pages", 1100)
+    _check(g, [g.n // 2 + 280, 0, g.n - 1] + list(range(1000, 1000 + 7 * (k - 3), 7)))
+
+
+def test_rows_taken_up_by_default():
+    """A box lattice: 6 neighbours at most, levels of up to 9,000 nodes."""
+    m = 110
+    i = np.arange(m ** 3).reshape(m, m, m)
+    pairs = [np.stack([a.ravel(), b.ravel()], 1) for a, b in ((i[1:], i[:-1]), (i[:, 1:], i[:, :-1]), (i[..., 1:], i[..., :-1]))]
+    _check(G.csr_from_edges(m ** 3, np.concatenate(pairs), "box"), [m ** 3 // 2 + 55, 0] + list(range(5, 5 + 14 * 90001, 90001)))
+
+
 def test_one_way_cycle(forced):
     """A CSR that is not symmetric (the caller's error): the pool is cleared every
     75,000 nodes, so the search comes round to nodes it no longer knows.  It ends
