@@ -2486,23 +2486,70 @@ static hipError_t launch_select_ell(int W, bool m8, hipStream_t s, int n, const 
 
 namespace ssm {
 
+// out: the longest row; of the first 8 arcs of the nodes on every 16th page,
+// those whose place in the next node's row names another page, and all of them.
+__global__ __launch_bounds__(256) void k_row_shape(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                   int* out) {
+    __shared__ int red[256 / kWave];
+    int longest = 0, moved = 0, seen = 0;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        const int e0 = rp[i], e1 = rp[i + 1];
+        longest = max(longest, e1 - e0);
+        if ((i >> kPageShift) % 16 == 0 && i + 1 < n) {
+            const int m = min(min(e1 - e0, rp[i + 2] - e1), 8);
+            for (int j = 0; j < m; ++j) moved += ci[e0 + j] >> kPageShift != ci[e1 + j] >> kPageShift;
+            seen += m;
+        }
+    }
+    longest = block_max(longest, red);
+    moved = block_sum(moved, red);
+    seen = block_sum(seen, red);
+    if (threadIdx.x == 0) {
+        atomicMax(&out[0], longest);
+        atomicAdd(&out[1], moved);
+        atomicAdd(&out[2], seen);
+    }
+}
+
+// Whether the rows go to k_bfs_ring.  Against k_bfs_grp's two workgroups per
+// row: 100 rows of a 3.25M-node mesh 30.3 against 37.3 ms, 16 rows 28.8 against
+// 29.5, 8 rows 29.6 against 27.9 (two workgroups have the memory to themselves):
+// from 16 rows on.  Rows of at most 8 entries (37.7 ms with padded rows of 16),
+// three on average (trees' levels are wide: 100 rows of a binary tree of 1.5M
+// nodes 11.5 against 11.0 ms), and a numbering that keeps neighbours of
+// neighbours in the order on a page (the same mesh with shuffled ids 56.1
+// against 55.0 ms): of the arcs compared at most one in eight moves to another
+// page.  A lattice numbered by rows has one in 128.
+static bool ring_pays(const ssm_csr* g, int32_t k, hipStream_t s) {
+    const int n = g->n;
+    if (sel_bits_fit(n) || k < 16 || g->nnz < 3LL * n || g->nnz > 8LL * n) return false;
+    int* d = nullptr;
+    if (salloc((void**)&d, sizeof(int) * 3) != SSM_OK) return false;
+    int h[3] = {};
+    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, d, 0, 3ll);
+    hipLaunchKernelGGL(k_row_shape, dim3(num_cus()), dim3(256), 0, s, n, g->row_ptr, g->col_idx, d);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(h, d, sizeof h, hipMemcpyDeviceToHost, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    sfree(d);
+    return e == hipSuccess && es == hipSuccess && h[0] <= 8 && 8LL * h[1] <= h[2];  // an error shows in the next call on s
+}
+
 // The k rows by k_bfs_ring; those it leaves are taken up by k_bfs_grp at the
 // level they reached (rows_resume).  *done stays false where the form does not
-// apply or its workspace cannot be had; the forms of mssp then run.  By default
-// for graphs whose visited bits do not fit in LDS and whose rows have at most 8
-// entries: 100 rows of a 3.25M-node mesh 37.3 -> 29.5 ms (37.7 with 16 slots per
-// padded row, so not above).  (tuning: bfs_ring -1 = never, 1 = any graph)
+// apply or its workspace cannot be had; the forms of mssp then run.  (tuning:
+// bfs_ring -1 = never, 1 = any graph of up to kPagedMaxN nodes)
 static ssm_status mssp_ring(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dist, int32_t* dmax_out_host,
                             bool* done, hipStream_t s) {
     const int n = g->n, forced = variant("bfs_ring");
-    if (forced != 1 && (forced < 0 || sel_bits_fit(n) || variant("bfs_ell") || variant("bfs_grp") ||
-                        variant("bfs_rowq") || variant("bfs_loads") || variant("bfs_lanes")))
+    if (n > kPagedMaxN || forced < 0) return SSM_OK;
+    if (forced != 1 && (variant("bfs_ell") || variant("bfs_grp") || variant("bfs_rowq") || variant("bfs_loads") ||
+                        variant("bfs_lanes") || variant("ell_width") > 8 || !ring_pays(g, k, s)))
         return SSM_OK;
     const int most = variant("bfs_pages");  // override: pages of the pool at most
     const Pages pg(n, most > 0 ? most : 65535);
     if (pg.count < 2 * kPagesSpare) return SSM_OK;
-    const int W = ell_width(g, s);
-    if (forced != 1 && W != 8) return SSM_OK;
+    const int W = forced == 1 ? ell_width(g, s) : 8;
     const int batch = (int)std::max<long long>(1, std::min<long long>(k, (1LL << 31) / (2LL * n)));
     int *ell = nullptr, *gq = nullptr, *aux = nullptr;  // aux: reached[k], from[k], ecc, stop
     const size_t aux_b = sizeof(int) * (2 * (size_t)k + 2);

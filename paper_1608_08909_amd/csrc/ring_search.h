@@ -15,29 +15,35 @@ enum RingState { kRsBytes = 0, kRsBits = 1, kRsFull = 2, kRsStamps = 3, kRsPaged
 
 // Paged visited bits.  A neighbour of level l lies on level l - 1, l or l + 1,
 // so the bits of the levels l - 1 and l and of the nodes claimed for l + 1
-// decide as the whole set would, and only the pages (2^shift ids) that those
+// decide as the whole set would, and only the pages (128 ids) that those
 // nodes lie in need bits.  A table of 16-bit entries names each page's bits in
 // a pool (0: none yet).  When the pool runs short, all of it is cleared and
 // the last two levels are put back.  A 3.25M-node mesh numbered by rows has up
-// to 4,000 pages of 128 ids in use and gains about 30 per level.  A search whose
+// to 4,000 pages in use and gains about 30 per level.  A search whose
 // last two levels alone fill the pool (wide levels, or a numbering that spreads
 // them) or whose next level finds it empty (the pool's second counter) is left
 // at its last complete level, the others of the launch soon after, and k_bfs_grp
 // takes the rows up from there.
 constexpr int kPagedBytes = 133120;  // table, pool and two counters: pages taken, pages refused
 constexpr int kPagesSpare = 512;     // pages kept free when a level starts
+constexpr int kPageShift = 7;        // log2 ids per page
+// Nodes whose page table is at most 53,248 bytes.  Larger graphs would need pages
+// of 256 ids, too few for their levels: 100 rows of a 6M-node lattice took 63.6 ms
+// with them, on two workgroups each 61.8.
+constexpr int kPagedMaxN = 3407488;
 
 struct Pages {
-    int shift, tab, count;  // log2 ids per page, table words, pages in the pool
+    int tab, count;  // table words, pages in the pool
     // `most` (tuning) takes fewer pages than fit.
-    __host__ explicit Pages(int n, int most = 65535) : shift(7) {
-        while ((((long long)n >> shift) + 2) * 2 > 53248) ++shift;
-        tab = ((n >> shift) + 2) / 2;
-        count = std::min((kPagedBytes / 4 - 2 - tab) >> (shift - 5), most);
-    }
-    __device__ Pages() : shift(5), tab(0), count(0) {}  // for the searches without pages
+    __host__ explicit Pages(int n, int most = 65535)
+        : tab(((n >> kPageShift) + 2) / 2), count(std::min((kPagedBytes / 4 - 2 - tab) >> (kPageShift - 5), most)) {}
+    __device__ Pages() : tab(0), count(0) {}  // for the searches without pages
     __device__ __forceinline__ unsigned* pool(unsigned* set) const { return set + 2 + tab; }
     __device__ __forceinline__ unsigned short* table(unsigned* set) const { return (unsigned short*)(set + 2); }
+    // The word of node u's bit in page e - 1 of the pool.
+    __device__ __forceinline__ unsigned* word(unsigned* set, int u, unsigned e) const {
+        return pool(set) + (((e - 1) << (kPageShift - 5)) + ((u & ((1 << kPageShift) - 1)) >> 5));
+    }
     // Clears everything (call with the whole workgroup, barriers around).
     __device__ __forceinline__ void clear(unsigned* set) const {
         for (int w = threadIdx.x; w < kPagedBytes / 4; w += blockDim.x) set[w] = 0u;
@@ -62,10 +68,10 @@ struct Pages {
     }
     // Marks node u, whose page has entry e: true if it was not marked (or has no page).
     __device__ __forceinline__ bool mark(unsigned* set, int u, unsigned e) const {
-        if (e == 0) e = take(set, u >> shift);
+        if (e == 0) e = take(set, u >> kPageShift);
         if (e == 0) return false;
         const unsigned bit = 1u << (u & 31);
-        return !(atomicOr(&pool(set)[((size_t)(e - 1) << (shift - 5)) + ((u & ((1 << shift) - 1)) >> 5)], bit) & bit);
+        return !(atomicOr(word(set, u, e), bit) & bit);
     }
 };
 
@@ -151,7 +157,7 @@ __device__ __forceinline__ void ring_claim(const int (&u)[N], bool (&ok)[N], int
 #pragma unroll
         for (int j = 0; j < N; ++j) {  // the entries in flight together
             ok[j] = (unsigned)u[j] < (unsigned)n;
-            e[j] = pg.table(bits)[ok[j] ? u[j] >> pg.shift : 0];
+            e[j] = pg.table(bits)[ok[j] ? u[j] >> kPageShift : 0];
         }
         bool any = false;
 #pragma unroll
@@ -160,18 +166,15 @@ __device__ __forceinline__ void ring_claim(const int (&u)[N], bool (&ok)[N], int
 #pragma unroll
             for (int j = 0; j < N; ++j)
                 if (ok[j] && e[j] == 0) {
-                    e[j] = pg.table(bits)[u[j] >> pg.shift];
-                    if (e[j] == 0) e[j] = pg.take(bits, u[j] >> pg.shift);
+                    e[j] = pg.table(bits)[u[j] >> kPageShift];
+                    if (e[j] == 0) e[j] = pg.take(bits, u[j] >> kPageShift);
                     ok[j] = e[j] != 0;
                 }
         }
         unsigned old[N];
 #pragma unroll
         for (int j = 0; j < N; ++j)
-            old[j] = ok[j] ? atomicOr(&pg.pool(bits)[((e[j] - 1) << (pg.shift - 5)) +
-                                                     ((u[j] & ((1 << pg.shift) - 1)) >> 5)],
-                                      1u << (u[j] & 31))
-                           : ~0u;
+            old[j] = ok[j] ? atomicOr(pg.word(bits, u[j], e[j]), 1u << (u[j] & 31)) : ~0u;
 #pragma unroll
         for (int j = 0; j < N; ++j) ok[j] = ok[j] && !(old[j] & (1u << (u[j] & 31)));
     } else {
@@ -340,7 +343,7 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
                 __syncthreads();
                 for (int pos = s_ls[nl - 1] + (int)threadIdx.x; pos < f.next; pos += blockDim.x) {
                     const int u = ring_get(f, q, pos);
-                    pg.mark(bits, u, pg.table(bits)[u >> pg.shift]);
+                    pg.mark(bits, u, pg.table(bits)[u >> kPageShift]);
                 }
                 __syncthreads();
                 leave = (int)bits[0] > pg.count - kPagesSpare;  // two levels alone fill the pool
