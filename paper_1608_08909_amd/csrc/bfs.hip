@@ -1494,6 +1494,38 @@ __device__ __forceinline__ bool sync_count(unsigned long long* bar, unsigned lon
     return s_go != 0;
 }
 
+// sync_count where some blocks run a whole search, of any number of levels,
+// while the others wait: the searches add kBeat to the counter every few levels,
+// the low 32 bits count the blocks (modulo 2^32), and `polls` polls without a
+// change in the rest give up.
+constexpr unsigned long long kBeat = 1ull << 32;
+
+__device__ __forceinline__ bool sync_search(unsigned long long* bar, unsigned& epoch, int blocks, int polls) {
+    __shared__ int s_go;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        epoch += blocks;
+        unsigned long long v = __hip_atomic_fetch_add(bar, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+        unsigned beat = (unsigned)(v >> 32);
+        int left = polls;
+        while ((v & kBarAbort) == 0 && (int)((unsigned)v - epoch) < 0) {
+            if (--left < 0) {
+                v = __hip_atomic_fetch_or(bar, kBarAbort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) | kBarAbort;
+                break;
+            }
+            v = __hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((unsigned)(v >> 32) != beat) {
+                beat = (unsigned)(v >> 32);
+                left = polls;
+            }
+        }
+        s_go = (v & kBarAbort) == 0;
+    }
+    __syncthreads();
+    return s_go != 0;
+}
+
 // The barrier over the whole grid (see sync_count).
 __device__ __forceinline__ bool sync_grid(unsigned long long* bar, unsigned long long& epoch) {
     return sync_count(bar, epoch, gridDim.x);
@@ -2620,8 +2652,9 @@ static hipError_t launch_select_ahead_t(hipStream_t s, int S, int n, const int* 
                                         int* gq, int* marks, unsigned long long* rec, int* ctl,
                                         unsigned long long* keys, int* status, unsigned long long* bar, int span) {
     int max_front = ahead_max_front(n);
+    int polls = variant("bar_polls") > 0 ? variant("bar_polls") : (int)kBarPolls;
     void* args[] = {&n,   &rp,  &ci,   &ell,    &t0,  &k, &first,     &pivots, &m, &lists, &gq, &marks,
-                    &rec, &ctl, &keys, &status, &bar, &S, &max_front, &span};
+                    &rec, &ctl, &keys, &status, &bar, &S, &max_front, &span, &polls};
     const int blocks = STATE == kRsStamps ? kAheadGroups + (kAheadMarks - 1) * kAheadMarkGroup
                                           : (S + kAheadMarks - 1) * kXcds;
     return hipLaunchCooperativeKernel((const void*)k_select_ahead<W, STATE>, dim3(blocks),

@@ -102,6 +102,7 @@ struct PlainRowSink {
 // 100k-node geometric graph.
 constexpr int kRingLevels = 128;  // levels between flushes at most
 constexpr int kRingStopLooks = 16;  // flushes between looks at the other searches' call to stop
+constexpr int kBeatLevels = 1024;   // levels between a search's signs of life
 constexpr int kRingLeft = -2;       // ring_search: left at a complete level, to be taken up from there
 constexpr int kRingPool = 155648;  // LDS of a search: long rows, visited set, queue
 
@@ -251,12 +252,14 @@ __device__ __forceinline__ int ring_wave_levels(int n, const int* __restrict__ r
 // as soon as a frontier is wider than `widest` or more than n nodes were found,
 // or kRingLeft where the pages ran out, which sets *stop, or *stop was set.
 // *end (thread 0): the largest distance (left: the last complete level, all of
-// it at the sink as well) and the nodes found.  Ends past a barrier.
+// it at the sink as well) and the nodes found.  beat: sync_search's counter, told
+// that the search goes on.  Ends past a barrier.
 template <int W, int STATE, class Sink>
 __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                             const int* __restrict__ ell, int src, int* q, int cap, int* lheavy,
                                             unsigned* bits, const int* m, Sink sink, int* gq, int widest = INT_MAX,
-                                            int2* end = nullptr, Pages pg = Pages(), int* stop = nullptr) {
+                                            int2* end = nullptr, Pages pg = Pages(), int* stop = nullptr,
+                                            unsigned long long* beat = nullptr) {
     __shared__ int2 s_slot[3];
     __shared__ int s_wave[4];
     __shared__ int s_ls[kRingLevels + 2];  // queue positions where the levels since the last flush start
@@ -366,6 +369,7 @@ __device__ __forceinline__ int ring_search(int n, const int* __restrict__ rp, co
                 __syncthreads();
                 return kRingLeft;
             }
+            if (beat && threadIdx.x == 0 && (d0 + nl) / kBeatLevels != d0 / kBeatLevels) atomicAdd(beat, kBeat);
             base += f.at;
             d0 += nl;
             nl = 0;

@@ -63,20 +63,25 @@ __host__ __device__ constexpr int ahead_block(int state) { return state == kRsSt
 // value above base + distance belongs to an older search, or to none, and
 // nothing is cleared between searches.  cnt: three counters that the levels
 // use in turn for the nodes they append, 0 on entry, with the source in place
-// and stamped.  bar: the group's barrier.  Returns the number of nodes found,
-// or -1 when a barrier was aborted.
+// and stamped.  bar: the group's barrier; beat: the counter of sync_search that
+// the other workgroups wait at.  Returns the number of nodes found, or -1 when a
+// barrier was aborted.
 template <int W, bool FULL>
 __device__ __forceinline__ int ahead_search_grp(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                 const int* __restrict__ ell, int G, int member, int* stamp, int base,
                                                 const int* m, unsigned long long* list, int* cnt,
-                                                unsigned long long* bar, unsigned long long& epoch) {
+                                                unsigned long long* bar, unsigned long long& epoch,
+                                                unsigned long long* beat) {
     constexpr int VW = W / 4;
     const int gt = member * (int)blockDim.x + (int)threadIdx.x, sub = gt % VW, grp = gt / VW,
               ngrp = G * (int)blockDim.x / VW;
     int at = 0, next = 1;
     for (int dv = 1; next > at; ++dv) {
         int* tail = &cnt[dv % 3];
-        if (gt == 0) store_agent(&cnt[(dv + 1) % 3], 0);  // last read two levels ago
+        if (gt == 0) {
+            store_agent(&cnt[(dv + 1) % 3], 0);  // last read two levels ago
+            if (dv % kBeatLevels == 0) atomicAdd(beat, kBeat);
+        }
         auto take = [&](const int (&u)[4]) {
             int old[4], mv[4];
             bool ok[4];
@@ -149,7 +154,7 @@ __device__ __forceinline__ int ahead_search_grp(int n, const int* __restrict__ r
 // list to its own bytes), a barrier (values below 127 come from the own bytes
 // and need none), each workgroup's argmax over its slice of the nodes, a
 // barrier.  The last pivot needs no search.  m, the lists, the rows and the
-// records pass between workgroups by agent-scope accesses alone, as sync_count
+// records pass between workgroups by agent-scope accesses alone, as sync_search
 // requires.  t0 = 0: from pivot `first` with m = infinity; t0 = 1: pivots 0
 // and 1 are known and m holds pivot 0's distances.  After pivot 0 the form
 // goes on alone only where it pays (status[1] = 0): a mean frontier
@@ -170,7 +175,7 @@ template <int W, int STATE>
 __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
     int n, const int* __restrict__ rp, const int* __restrict__ ci, const int* __restrict__ ell, int t0, int k,
     int first, int* pivots, int* m, unsigned long long* lists, int* gq, int* marks, unsigned long long* rec, int* ctl,
-    unsigned long long* keys, int* status, unsigned long long* bar, int S, int max_front, int span) {
+    unsigned long long* keys, int* status, unsigned long long* bar, int S, int max_front, int span, int polls) {
     constexpr int kBlk = ahead_block(STATE);
     constexpr int R = 8;            // records per thread
     constexpr int kRec = R * kBlk;  // records kept per round
@@ -224,8 +229,8 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
             }
             unsigned long long* bf = gbar(kAheadMax + f);
             if (!sync_count(bf, gepoch, GL)) return;
-            if (ahead_search_grp<W, true>(n, rp, ci, ell, GL, member, row, 0, m, list, gcnt(kAheadMax + f), bf, gepoch) <
-                0)
+            if (ahead_search_grp<W, true>(n, rp, ci, ell, GL, member, row, 0, m, list, gcnt(kAheadMax + f), bf, gepoch,
+                                          bar) < 0)
                 return;
         } else {
             ring_search<W, kRsFull>(n, rp, ci, ell, src, lq, cap, lheavy, bits, m, RowSink{row}, myq);
@@ -235,10 +240,10 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
         if (member == 0 && tid == 0) atomicOr(&ctl[kAcReady], 1 << f);
         return;
     }
-    unsigned long long epoch = 0;
+    unsigned epoch = 0;
 #define SYNC_OR_LEAVE()                               \
     do {                                              \
-        if (!sync_count(bar, epoch, NB)) {            \
+        if (!sync_search(bar, epoch, NB, polls)) {    \
             if (lead) {                               \
                 store_agent(&status[2], 1);           \
                 store_agent(&ctl[kAcKnown], kAcOver); \
@@ -471,9 +476,9 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
                     int len = -1;
                     if (sync_count(gbar(q), gepoch, gsize))
                         len = src == p ? ahead_search_grp<W, true>(n, rp, ci, ell, gsize, member, m, 0, m, list,
-                                                                   gcnt(q), gbar(q), gepoch)
+                                                                   gcnt(q), gbar(q), gepoch, bar)
                                        : ahead_search_grp<W, false>(n, rp, ci, ell, gsize, member, stamp, base, m,
-                                                                    list, gcnt(q), gbar(q), gepoch);
+                                                                    list, gcnt(q), gbar(q), gepoch, bar);
                     if (len < 0) {  // aborted
                         if (tid == 0) {
                             store_agent(&status[2], 1);
@@ -488,7 +493,8 @@ __global__ __launch_bounds__(ahead_block(STATE)) void k_select_ahead(
             } else if (fresh >> b & 1) {
                 const int len = ring_search<W, STATE>(n, rp, ci, ell, s_cid[b], lq, cap, lheavy, bits, m,
                                                        ListSink{lists + (size_t)b * n}, myq,
-                                                       t == 0 && max_front < INT_MAX / 2 ? 2 * max_front : INT_MAX);
+                                                       t == 0 && max_front < INT_MAX / 2 ? 2 * max_front : INT_MAX,
+                                                       nullptr, Pages(), nullptr, bar);
                 if (tid == 0) store_agent(&ctl[kAcLen + b], len);
             }
             SYNC_OR_LEAVE();
