@@ -401,7 +401,8 @@ void ssm_release_cache(void);
  *   select_ahead -1|N (no searches ahead of their turn, or N workgroups of
  *   them whatever the graph's size, as far as its visited bits fit in LDS),
  *   bar_polls N (polls without a sign of life after which the barrier between
- *   searches ahead gives up),
+ *   searches ahead gives up), ahead_cus N (compute units that their launch may
+ *   count on),
  *   select_blocks N, select_threads 256|512, select_ell 2 (plain CSR),
  *   select_m8 2 (no LDS byte copy), select_rowq 2, select_pre 1|3,
  *   select_wave -1|2 (block levels only, two passes per wave level),

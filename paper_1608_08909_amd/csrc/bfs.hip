@@ -2646,23 +2646,15 @@ static int ahead_max_front(int n) {
     return variant("select_ahead") > 0 ? INT_MAX : (int)(2.0 * std::sqrt((double)n));
 }
 
-template <int W, int STATE>
-static hipError_t launch_select_ahead_t(hipStream_t s, int S, int n, const int* rp, const int* ci, const int* ell,
-                                        int t0, int k, int first, int* pivots, int* m, unsigned long long* lists,
-                                        int* gq, int* marks, unsigned long long* rec, int* ctl,
-                                        unsigned long long* keys, int* status, unsigned long long* bar, int span) {
-    int max_front = ahead_max_front(n);
-    int polls = variant("bar_polls") > 0 ? variant("bar_polls") : (int)kBarPolls;
-    void* args[] = {&n,   &rp,  &ci,   &ell,    &t0,  &k, &first,     &pivots, &m, &lists, &gq, &marks,
-                    &rec, &ctl, &keys, &status, &bar, &S, &max_front, &span, &polls};
-    const int blocks = STATE == kRsStamps ? kAheadGroups + (kAheadMarks - 1) * kAheadMarkGroup
-                                          : (S + kAheadMarks - 1) * kXcds;
-    return hipLaunchCooperativeKernel((const void*)k_select_ahead<W, STATE>, dim3(blocks),
-                                      dim3(ahead_block(STATE)), args, 0, s);
+template <int STATE>
+static const void* ahead_kernel(int W) {
+    return W == 8 ? (const void*)k_select_ahead<8, STATE> : W == 16 ? (const void*)k_select_ahead<16, STATE>
+                                                                     : (const void*)k_select_ahead<32, STATE>;
 }
 
 // Pivots t0 .. k-1 with searches run ahead on S workers (k_select_ahead);
-// *ran stays false, with nothing enqueued, when its workspace cannot be had.
+// *ran stays false, with nothing enqueued, when its workspace cannot be had or
+// its workgroups are not resident together (a device of few CUs).
 // ecc: pivot 0's eccentricity (t0 = 1).  bar: a zeroed 64-bit barrier counter
 // for this launch alone.  *work: its workspace, for sfree once the stream is
 // idle.
@@ -2674,6 +2666,17 @@ static hipError_t select_ahead(const ssm_csr* g, int S, int W, const int* ell, i
     const bool stamps = t0 == 1 && (!sel_bits_fit(n) || variant("select_m8") == 3);
     const long long span = 2ll * ecc + 4;  // above any distance
     if ((!stamps && !sel_bits_fit(n)) || (stamps && span * (k + 1ll) >= INT_MAX)) return hipSuccess;
+    const bool bytes = t0 == 0 && sel_m8_fits(n) && variant("select_m8") != 2;
+    const void* kern = stamps ? ahead_kernel<kRsStamps>(W) : bytes ? ahead_kernel<kRsBytes>(W) : ahead_kernel<kRsBits>(W);
+    const int block = ahead_block(stamps ? kRsStamps : kRsBits);
+    const int blocks = stamps ? kAheadGroups + (kAheadMarks - 1) * kAheadMarkGroup : (S + kAheadMarks - 1) * kXcds;
+    const int cus = variant("ahead_cus") > 0 ? variant("ahead_cus") : num_cus();  // override: CUs to count on
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return hipSuccess;
+    }
+    if ((long long)blocks > (long long)per_cu * cus) return hipSuccess;
     const size_t lists_b = 8 * nn * (S + kAheadMarks - 1), rec_b = 16 * (size_t)kAheadRec,
                  gq_b = (stamps ? 4 * nn * S : 8 * nn * (S + kAheadMarks - 1)), marks_b = 4 * nn * kAheadMarks;
     if (salloc(work, lists_b + rec_b + gq_b + marks_b + 4 * kAcInts) != SSM_OK) {
@@ -2694,24 +2697,12 @@ static hipError_t select_ahead(const ssm_csr* g, int S, int W, const int* ell, i
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const bool bytes = t0 == 0 && sel_m8_fits(n) && variant("select_m8") != 2;
-#define SSM_AHEAD(W_, ST_)                                                                                      \
-    return launch_select_ahead_t<W_, ST_>(s, S, n, g->row_ptr, g->col_idx, ell, t0, k, first, pivots, m, lists, \
-                                              gq, marks, rec, ctl, keys, status, bar, (int)span)
-    if (stamps) {
-        if (W == 8) SSM_AHEAD(8, kRsStamps);
-        if (W == 16) SSM_AHEAD(16, kRsStamps);
-        SSM_AHEAD(32, kRsStamps);
-    }
-    if (bytes) {
-        if (W == 8) SSM_AHEAD(8, kRsBytes);
-        if (W == 16) SSM_AHEAD(16, kRsBytes);
-        SSM_AHEAD(32, kRsBytes);
-    }
-    if (W == 8) SSM_AHEAD(8, kRsBits);
-    if (W == 16) SSM_AHEAD(16, kRsBits);
-    SSM_AHEAD(32, kRsBits);
-#undef SSM_AHEAD
+    int max_front = ahead_max_front(n), span_i = (int)span;
+    int polls = variant("bar_polls") > 0 ? variant("bar_polls") : (int)kBarPolls;
+    const int *rp = g->row_ptr, *ci = g->col_idx;
+    void* args[] = {(void*)&n, &rp, &ci, &ell,    &t0,   &k,   &first, &pivots,    &m,      &lists, &gq,
+                    &marks,    &rec, &ctl, &keys, &status, &bar, &S,   &max_front, &span_i, &polls};
+    return hipLaunchCooperativeKernel(kern, dim3(blocks), dim3(block), args, 0, s);
 }
 
 template <int VW, bool ROWQ, int PRE>

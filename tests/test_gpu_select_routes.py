@@ -28,3 +28,13 @@ def test_a_search_longer_than_the_barrier_waits(n, state, forced):
     forced("select_m8", state)
     forced("bar_polls", 30000)
     _check(G.path(n), 4)
+
+
+@pytest.mark.parametrize("state,n", [(0, 41000), (2, 41000), (2, 264000), (3, 264000)])
+@pytest.mark.parametrize("cus", [1, 8, 31])
+def test_few_compute_units(cus, state, n, forced):
+    """Where the searches' workgroups are not resident together, the other forms select."""
+    forced("select_ahead", 16)
+    forced("select_m8", state)
+    forced("ahead_cus", cus)
+    _check(G.grid(n // 200, 200), 12)
