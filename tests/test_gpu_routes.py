@@ -1,5 +1,6 @@
 """The route a call takes by default is not slower than the one it can be made to
 take instead (the faster of several runs of each, with room for their spread)."""
+import threading
 import time
 
 import numpy as np
@@ -51,3 +52,26 @@ def test_rows_of_a_mesh_too_large_for_the_pages():
     g = _lattice(1900, 1895)
     piv = torch.from_numpy(np.random.default_rng(7).choice(g.n, 40, replace=False).astype(np.int32)).cuda()
     _compare("40 rows", lambda: ssm.bfs_pivots(g, piv), {"bfs_ring": -1}, 1.15)
+
+
+def test_selections_of_several_threads():
+    """Each on a stream of its own: together as fast as on one workgroup each."""
+    graphs = [_lattice(300, 300 + q) for q in range(4)]
+    streams = [torch.cuda.Stream() for _ in graphs]
+    want = [ssm.select_pivots(g, 100) for g in graphs]
+    got = [None] * len(graphs)
+
+    def work(q):
+        with torch.cuda.stream(streams[q]):
+            for _ in range(3):
+                got[q] = ssm.select_pivots(graphs[q], 100)
+
+    def all_threads():
+        threads = [threading.Thread(target=work, args=(q,)) for q in range(len(graphs))]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+
+    _compare("4 threads", all_threads, {"select_ahead": -1}, 1.3)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
