@@ -604,18 +604,27 @@ __global__ __launch_bounds__(256) void k_max_degree(int n, const int* __restrict
     if (lane_id() == 0 && d > 0) atomicMax(out, d);
 }
 
-// Slots per padded row: 8 for a mean degree up to 4 and wherever no row is
-// longer than 8 (a level's work goes with the slots, the unused ones too: on a
-// 150k-node mesh of degree 6 the selection takes 8.6 ms with 8 slots against
-// 10.5 ms with 16, the rows 1.7 against 2.1 ms), else 16 up to 12 and 32 above
-// (with 8 slots and rows of up to 22, a 100k-node geometric graph's selection
-// goes 9.0 -> 16.8 ms).  Synchronizes for a mean degree in (4, 8].
-static int ell_width(const ssm_csr* g, hipStream_t s) {
+// Slots per padded row by the mean degree: 8 up to 4, 16 up to 12, 32 above.
+// k_select_grid takes these: with fewer lanes per node its levels take longer
+// (mesh of 1.2M nodes with rows of at most 6, k = 8: 25.4 ms with 16 slots, 29.9
+// with 8).
+static int mean_width(const ssm_csr* g) {
     const int forced = variant("ell_width");  // tuning override: 8, 16 or 32
     if (forced == 8 || forced == 16 || forced == 32) return forced;
     const double avg = g->n > 0 ? (double)g->nnz / g->n : 0.0;
-    if (avg <= 4.0) return 8;
-    if (avg > 12.0) return 32;
+    return avg <= 4.0 ? 8 : avg <= 12.0 ? 16 : 32;
+}
+
+// The searches of one workgroup: 8 slots also wherever no row is longer than 8 (a
+// level's work goes with the slots, the unused ones too: on a 150k-node mesh of
+// degree 6 the selection takes 8.6 ms with 8 slots against 10.5 ms with 16, the
+// rows 1.7 against 2.1 ms; with 8 slots and rows of up to 22, a 100k-node
+// geometric graph's selection goes 9.0 -> 16.8 ms).  Synchronizes for a mean
+// degree in (4, 8].
+static int ell_width(const ssm_csr* g, hipStream_t s) {
+    const int w = mean_width(g), forced = variant("ell_width");
+    if (w != 16 || forced == 16) return w;
+    const double avg = (double)g->nnz / g->n;
     int* d = nullptr;
     if (avg > 8.0 || salloc((void**)&d, sizeof(int)) != SSM_OK) return 16;
     int most = 0;
@@ -2920,7 +2929,7 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
     int* ell = nullptr;
     void* awork = nullptr;  // workspace of the searches run ahead
     const bool use_ell = mode == 1 && sel_bits_fit(n) && variant("select_ell") != 2;
-    const int W = use_ell || mode == 4 ? ell_width(g, s) : 0;
+    const int W = use_ell ? ell_width(g, s) : mode == 4 ? mean_width(g) : 0;
     const int ahead = variant("select_mode") == 0 && variant("select_ell") != 2 ? ahead_workers(n, k) : 0;
     if (use_ell && e == hipSuccess) {
         st = salloc((void**)&ell, sizeof(int) * (size_t)n * W);
@@ -3008,9 +3017,14 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
                 }
             } else {
                 bool ran = false;
-                if (ahead && mean_front <= ahead_max_front(n))
-                    e = select_ahead(g, ahead, W, ell, 1, hs[1], k, first, pivots, m, keys, status, bars + 16, &awork, &ran,
-                                     s);
+                if (ahead && mean_front <= ahead_max_front(n)) {
+                    const int Wa = ell_width(g, s);  // at most W: the padded rows' buffer serves both
+                    if (Wa != W) e = ell_build(g, Wa, ell, s);
+                    if (e == hipSuccess)
+                        e = select_ahead(g, ahead, Wa, ell, 1, hs[1], k, first, pivots, m, keys, status, bars + 16,
+                                         &awork, &ran, s);
+                    if (e == hipSuccess && !ran && Wa != W) e = ell_build(g, W, ell, s);
+                }
                 int b1 = mean_front < 4096.0 ? std::min(b0, kSelGridBlocks / 2) : b0;
                 if (variant("select_blocks") > 0) b1 = std::min(gmax, variant("select_blocks"));
                 b1 = std::max(1, std::min(b1, gmax));

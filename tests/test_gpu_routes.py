@@ -75,3 +75,10 @@ def test_selections_of_several_threads():
 
     _compare("4 threads", all_threads, {"select_ahead": -1}, 1.3)
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_grid_selection_width():
+    """The grid's levels with the rows padded as its lanes want them."""
+    g = _lattice(1095, 1095)
+    with ssm.variants(select_ahead=-1):
+        _compare("grid, k = 8", lambda: ssm.select_pivots(g, 8), {"ell_width": 16}, 1.06, reps=8)
