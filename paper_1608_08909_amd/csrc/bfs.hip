@@ -597,11 +597,26 @@ __global__ void k_ell_build(int n, int W, const int* __restrict__ rp, const int*
 }
 
 __global__ __launch_bounds__(256) void k_max_degree(int n, const int* __restrict__ rp, int* out) {
+    __shared__ int red[256 / kWave];
     int d = 0;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
         d = max(d, rp[i + 1] - rp[i]);
-    d = wave_max(d);
-    if (lane_id() == 0 && d > 0) atomicMax(out, d);
+    d = block_max(d, red);
+    if (threadIdx.x == 0 && d > 0) atomicMax(out, d);
+}
+
+// The longest row, or -1 (an error shows in the next call on s).  Synchronizes.
+static int longest_row(const ssm_csr* g, hipStream_t s) {
+    int* d = nullptr;
+    if (salloc((void**)&d, sizeof(int)) != SSM_OK) return -1;
+    int most = 0;
+    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, d, 0, 1ll);
+    hipLaunchKernelGGL(k_max_degree, dim3(std::min(div_up(g->n, 1024), num_cus())), dim3(256), 0, s, g->n, g->row_ptr, d);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(&most, d, sizeof(int), hipMemcpyDeviceToHost, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    sfree(d);
+    return e == hipSuccess && es == hipSuccess ? most : -1;
 }
 
 // Slots per padded row by the mean degree: 8 up to 4, 16 up to 12, 32 above.
@@ -620,21 +635,12 @@ static int mean_width(const ssm_csr* g) {
 // degree 6 the selection takes 8.6 ms with 8 slots against 10.5 ms with 16, the
 // rows 1.7 against 2.1 ms; with 8 slots and rows of up to 22, a 100k-node
 // geometric graph's selection goes 9.0 -> 16.8 ms).  Synchronizes for a mean
-// degree in (4, 8].
-static int ell_width(const ssm_csr* g, hipStream_t s) {
+// degree in (4, 8], unless the longest row is given.
+static int ell_width(const ssm_csr* g, hipStream_t s, int longest = -1) {
     const int w = mean_width(g), forced = variant("ell_width");
-    if (w != 16 || forced == 16) return w;
-    const double avg = (double)g->nnz / g->n;
-    int* d = nullptr;
-    if (avg > 8.0 || salloc((void**)&d, sizeof(int)) != SSM_OK) return 16;
-    int most = 0;
-    hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(64), 0, s, d, 0, 1ll);
-    hipLaunchKernelGGL(k_max_degree, dim3(std::min(div_up(g->n, 1024), 1024)), dim3(256), 0, s, g->n, g->row_ptr, d);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(&most, d, sizeof(int), hipMemcpyDeviceToHost, s);
-    const hipError_t es = hipStreamSynchronize(s);
-    sfree(d);
-    return e == hipSuccess && es == hipSuccess && most <= 8 ? 8 : 16;  // an error shows in the next call on s
+    if (w != 16 || forced == 16 || g->nnz > 8LL * g->n) return w;
+    if (longest < 0) longest = longest_row(g, s);
+    return longest >= 0 && longest <= 8 ? 8 : 16;
 }
 
 static hipError_t ell_build(const ssm_csr* g, int W, int* ell, hipStream_t s) {
@@ -2637,13 +2643,41 @@ static ssm_status mssp_ring(const ssm_csr* g, int32_t k, const int32_t* pivots, 
     return SSM_OK;
 }
 
-// Searches run ahead: workers for a graph of n nodes and k pivots (0: the
-// form does not apply).
-static int ahead_workers(int n, int k) {
+// One workgroup up to this many nodes (its levels cost no grid barrier); the
+// cooperative grid above (frontiers too wide for one workgroup).
+constexpr long long kSelOneWgMaxN = 1LL << 18;
+
+// Searches run ahead: workers for a graph and k pivots (0: the form does not
+// apply).  A selection begins with searches that nothing foretells, each a round
+// of its own, so the form pays from a number of pivots on, against one workgroup
+// (up to 2^18 nodes, about 140k of them with the byte copy of m; ms, one
+// workgroup -> ahead):
+//   meshes (mean degree 6)   41k: k = 16 2.07 -> 2.22, 32 2.79 -> 2.52; 132k: k = 32
+//                            6.36 -> 6.64, 48 7.28 -> 7.17; 250k: k = 12 7.37 -> 7.80,
+//                            24 9.96 -> 8.42
+//   geometric (degree 8)     41k: k = 16 2.15 -> 2.24, 32 2.81 -> 2.66; 132k: k = 16
+//                            6.46 -> 7.15, 32 8.00 -> 7.68; 160k: 24 8.75 -> 7.88
+//   lattices (degree 4)      41k: k = 64 3.99 -> 4.09, 100 4.83 -> 4.65; 132k: k = 32
+//                            6.77 -> 7.13, 64 8.68 -> 8.39; 250k: k = 24 10.4 -> 10.8,
+//                            32 12.2 -> 11.6
+// and against the grid above: mesh of 300k, k = 8 10.9 -> 8.2; 1.2M 25.4 -> 27.1,
+// k = 16 36.4 -> 31.8; 3.25M k = 8 45.0 -> 46.3, k = 16 63.5 -> 59.2.  Trees and
+// chains (mean degree about 2) are not foretold and hub graphs (a row above 64;
+// geometric graphs have rows of up to 30) have wide levels: a start of the form
+// would cost them 0.1 ms (41k nodes, k = 24: tree 0.94 -> 1.05, preferential
+// attachment 0.68 -> 0.76).
+static int ahead_workers(const ssm_csr* g, int k) {
+    const int n = g->n;
     const int v = variant("select_ahead");  // override: -1 never, else the workers
     if (v < 0 || k < 2) return 0;
     if (v > 0) return std::min(v, sel_bits_fit(n) ? kAheadMax : kXcds);
-    return n >= kAheadMinN && k >= 8 ? kAheadWorkers : 0;
+    if (n < kAheadMinN || g->nnz < 3LL * n) return 0;
+    int least = sel_bits_fit(n) ? 8 : 16;
+    if (n <= kSelOneWgMaxN) {
+        const bool lattice = 2LL * g->nnz < 9LL * n;  // a mean degree below 4.5
+        least = !sel_m8_fits(n) ? (lattice ? 32 : 24) : g->nnz >= 7LL * n ? 24 : lattice ? 96 : 48;
+    }
+    return k >= least ? kAheadWorkers : 0;
 }
 
 // The widest mean frontier (of pivot 0's BFS) with which searches run ahead:
@@ -2866,9 +2900,6 @@ static int select_max_blocks() {
     return std::max(1, std::min(a, b)) * num_cus();
 }
 
-// One workgroup up to this many nodes (its levels cost no grid barrier); the
-// cooperative grid above (frontiers too wide for one workgroup).
-constexpr long long kSelOneWgMaxN = 1LL << 18;
 constexpr int kSelGridBlocks = 32;
 constexpr int kSelHybBlocks = 64;  // grid of the hybrid form (its blocks only share the argmax)
 
@@ -2929,8 +2960,10 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
     int* ell = nullptr;
     void* awork = nullptr;  // workspace of the searches run ahead
     const bool use_ell = mode == 1 && sel_bits_fit(n) && variant("select_ell") != 2;
-    const int W = use_ell ? ell_width(g, s) : mode == 4 ? mean_width(g) : 0;
-    const int ahead = variant("select_mode") == 0 && variant("select_ell") != 2 ? ahead_workers(n, k) : 0;
+    int ahead = variant("select_mode") == 0 && variant("select_ell") != 2 ? ahead_workers(g, k) : 0;
+    const int longest = ahead && variant("select_ahead") == 0 ? longest_row(g, s) : -1;
+    if (longest > kAheadMaxRow) ahead = 0;
+    const int W = use_ell ? ell_width(g, s, longest) : mode == 4 ? mean_width(g) : 0;
     if (use_ell && e == hipSuccess) {
         st = salloc((void**)&ell, sizeof(int) * (size_t)n * W);
         if (st != SSM_OK) {
@@ -3018,7 +3051,7 @@ ssm_status select_pivots(const ssm_csr* g, int32_t k, int32_t first, int32_t* pi
             } else {
                 bool ran = false;
                 if (ahead && mean_front <= ahead_max_front(n)) {
-                    const int Wa = ell_width(g, s);  // at most W: the padded rows' buffer serves both
+                    const int Wa = ell_width(g, s, longest);  // at most W: the padded rows' buffer serves both
                     if (Wa != W) e = ell_build(g, Wa, ell, s);
                     if (e == hipSuccess)
                         e = select_ahead(g, ahead, Wa, ell, 1, hs[1], k, first, pivots, m, keys, status, bars + 16,

@@ -37,8 +37,8 @@ constexpr int kAheadMax = 16;      // workers at most
 constexpr int kAheadWorkers = 8;   // by default
 // Smallest graph: below, a round's overhead (about 40 us for the guess, 8 us
 // per pivot) eats the levels saved: a 30k-node lattice, k = 60, 3.5 against
-// 3.4 ms; a 50k-node mesh, k = 150, 5.8 against 7.0 ms.
-constexpr int kAheadMinN = 40000;
+// 3.4 ms.
+constexpr int kAheadMinN = 40000, kAheadMaxRow = 64;
 // where the visited bits do not fit in LDS: the workers' workgroups, of one search at most, of a landmark's
 constexpr int kAheadGroups = 32, kAheadGroupMax = 16, kAheadMarkGroup = 8;
 constexpr int kXcds = 8;           // workgroups of a launch go to the XCDs in turn

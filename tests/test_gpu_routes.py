@@ -82,3 +82,8 @@ def test_grid_selection_width():
     g = _lattice(1095, 1095)
     with ssm.variants(select_ahead=-1):
         _compare("grid, k = 8", lambda: ssm.select_pivots(g, 8), {"ell_width": 16}, 1.06, reps=8)
+
+
+def test_selection_of_few_pivots():
+    g = _lattice(300, 300)
+    _compare("k = 8", lambda: ssm.select_pivots(g, 8), {"select_ahead": -1}, 1.12, reps=8)

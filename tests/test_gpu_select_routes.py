@@ -38,3 +38,33 @@ def test_few_compute_units(cus, state, n, forced):
     forced("select_m8", state)
     forced("ahead_cus", cus)
     _check(G.grid(n // 200, 200), 12)
+
+
+def _regular(n, seed):
+    """Four random cycles: 8 neighbours, and levels that soon hold most nodes."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    cycles = [rng.permutation(n) for _ in range(4)]
+    return G.csr_from_edges(n, np.concatenate([np.stack([c, np.roll(c, -1)], 1) for c in cycles]), "regular")
+
+
+def _layers(layers, width, seed):
+    """Layers of `width` nodes, three random arcs from each node to the next layer."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    u = np.arange((layers - 1) * width)
+    v = (u // width + 1)[:, None] * width + rng.integers(0, width, (u.size, 3))
+    last = np.stack([np.arange(u.size, u.size + width), u.size - width + np.arange(width)], 1)
+    return G.csr_from_edges(layers * width, np.concatenate([np.stack([np.repeat(u, 3), v.ravel()], 1), last]), "layers")
+
+
+RULE = [(G.grid(205, 200), 95), (G.grid(205, 200), 96), (G.tri_grid(205, 200), 47), (G.tri_grid(205, 200), 48),
+        (G.rgg(42000, 3, 8.0), 23), (G.rgg(42000, 3, 8.0), 24), (G.tri_grid(199, 200), 60),
+        (G.barabasi_albert(42000, 5, 2), 30), (G.tree_plus(42000, 5), 120), (_regular(42000, 1), 30),
+        (_layers(100, 420, 2), 60), (G.grid(400, 390), 31), (G.grid(400, 390), 32),
+        (G.tri_grid(400, 390), 23), (G.tri_grid(400, 390), 24), (G.tri_grid(520, 530), 7),
+        (G.tri_grid(520, 530), 8), (G.rgg(280000, 3, 8.0), 8), (_regular(270000, 1), 8)]
+
+
+@pytest.mark.parametrize("g,k", RULE, ids=[f"{g.name}-{k}" for g, k in RULE])
+def test_rule(g, k):
+    """Both sides of the default rule's lines, and graphs that leave the form again."""
+    _check(g, k)
