@@ -416,7 +416,8 @@ void ssm_release_cache(void);
  *   bfs_lanes 2..64, msbfs -1|1 (never / always the bit-parallel BFS
  *   first; by default it goes first on graphs of at least 2^19 arcs whose
  *   mean neighbour degree is at least 3x their mean degree), msbfs_budget N,
- *   region_mode 1|2, km_chunk 32|40|48|56|64,
+ *   region_mode 1|2, km_chunk 32|40|48|56|64, km_matrix -1|1 (k-means sp on
+ *   the vector units, or on the matrix units whatever k),
  *   sweep_mode 1|2 (LDS histograms, global table), sweep_split 1|2|4,
  *   sweep_blocks_per_cu N, sweep_waves 4|16 (waves per block),
  *   sweep_tune -1 (no timing of launch shapes: the rule shape; the FP32

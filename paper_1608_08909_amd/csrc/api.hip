@@ -139,7 +139,7 @@ const char* const kVariantNames[] = {
     "select_wave", "select_rowq",   "select_pre",    "select_blocks", "select_mode",  "select_ell", "select_hyb", "select_ahead",
     "select_m8",   "region_mode",   "km_chunk",      "sweep_perm",    "sweep_mode",   "sweep_split",
     "sweep_blocks_per_cu", "sweep_waves", "sweep_tune", "sssp_nearfar", "sssp_band", "ell_width", "pool_graph", "pool_persist", "pool_follow", "sweep_f64_terms", "sweep_f64_hubs", "bfs_loads", "bfs_grp", "bfs_ring",
-    "bfs_pages", "bar_polls", "ahead_cus"};
+    "bfs_pages", "bar_polls", "ahead_cus", "km_matrix"};
 }  // namespace
 
 int variant(const char* name, int unset) {

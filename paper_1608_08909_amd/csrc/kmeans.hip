@@ -19,8 +19,8 @@
 // cluster operand comes from scalar loads, one node per lane, C clusters
 // per block.  Every product and partial sum is an integer below 2^53, so the
 // FMAs are exact in any order.  The assignment itself runs on the 8-bit matrix
-// instructions wherever the distances and sums split into few digits
-// (k_km_assign_mx); the passes follow one another on the device, a flag ending
+// instructions from kKmMatrixMinK pivots on, wherever the distances and sums
+// split into few digits (k_km_assign_mx); the passes follow one another on the device, a flag ending
 // them, and the host looks at it every kKmBatch passes.
 #include <stdlib.h>
 
@@ -37,6 +37,11 @@ constexpr int kKmChunk = 32;   // clusters per block of the nearest-node kernel
 constexpr int kKmPad = 64;     // zero doubles after the sums: the widest chunk may read that far past row k-1
 constexpr int kKmMaxK = 4096;  // the sums' partial tables are (k + 1) k words per node range
 constexpr int kKmMinBlocks = 2048;
+// Pivots from which the matrix form is taken: its tiles hold 64 features and 16
+// clusters, so small k pay for padding.  50 passes, vector against matrix form:
+// 50k nodes k = 16 1.76 / 1.95 ms, 48 2.40 / 2.34, 64 2.77 / 2.53; 1M nodes k = 3
+// (38 passes) 2.44 / 4.65, 24 9.7 / 10.4, 48 19.4 / 16.8.
+constexpr int kKmMatrixMinK = 48;
 constexpr int kKmBatch = 4;    // passes enqueued between looks at the flag
 // control words: nodes moved in the pass, no node moved (the later passes return at once), passes run
 constexpr int kKmMoved = 0, kKmDone = 1, kKmPasses = 2, kKmCtl = 4;
@@ -404,7 +409,7 @@ static hipError_t km_assign_mx(int n, int k, int nkb, int kc, const uint4* Y, co
     return hipGetLastError();
 }
 
-// Built for LS in 2 .. 6.
+// Built for LS in 2 .. 5.
 template <int LS>
 static hipError_t km_commit_mx(int k, int nkb, int kc, const unsigned long long* S2, double* ST, double* N, uint4* Sq,
                                int* ctl, hipStream_t s) {
@@ -623,9 +628,11 @@ ssm_status kmeans_pivots(int32_t n, int32_t k, const int32_t* pivots, const int3
         dmax = hdm;
     }
     // the matrix form's digits; other counts (distances above 32,639, sums
-    // above 2^47) take the vector form, as does a forced km_chunk
+    // above 5.4e11) take the vector form, as does a forced km_chunk (tuning:
+    // km_matrix -1 = never, 1 = whatever k)
     const int ly = km_digit_count(dmax), ls = std::max(2, km_digit_count((double)n * dmax));
-    bool mx = ly <= 2 && ls <= 6 && variant("km_chunk") == 0;
+    const int forced = variant("km_matrix");
+    bool mx = ly <= 2 && ls <= 5 && variant("km_chunk") == 0 && forced >= 0 && (forced == 1 || k >= kKmMatrixMinK);
     const int nkb = div_up(k, 64) * 4, kc = div_up(k, 16) * 16;
     // launch shapes
     const int nb = div_up(n, kKmBlock);
@@ -714,8 +721,7 @@ ssm_status kmeans_pivots(int32_t n, int32_t k, const int32_t* pivots, const int3
             case 2: return km_commit_mx<2>(k, nkb, kc, sums, ST, N, Sq, ctl, s);
             case 3: return km_commit_mx<3>(k, nkb, kc, sums, ST, N, Sq, ctl, s);
             case 4: return km_commit_mx<4>(k, nkb, kc, sums, ST, N, Sq, ctl, s);
-            case 5: return km_commit_mx<5>(k, nkb, kc, sums, ST, N, Sq, ctl, s);
-            default: return km_commit_mx<6>(k, nkb, kc, sums, ST, N, Sq, ctl, s);
+            default: return km_commit_mx<5>(k, nkb, kc, sums, ST, N, Sq, ctl, s);
         }
     };
     auto assign_mx = [&]() {
@@ -726,8 +732,7 @@ ssm_status kmeans_pivots(int32_t n, int32_t k, const int32_t* pivots, const int3
             case 2: SSM_KM(2);
             case 3: SSM_KM(3);
             case 4: SSM_KM(4);
-            case 5: SSM_KM(5);
-            default: SSM_KM(6);
+            default: SSM_KM(5);
         }
 #undef SSM_KM
     };

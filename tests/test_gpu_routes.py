@@ -87,3 +87,9 @@ def test_grid_selection_width():
 def test_selection_of_few_pivots():
     g = _lattice(300, 300)
     _compare("k = 8", lambda: ssm.select_pivots(g, 8), {"select_ahead": -1}, 1.12, reps=8)
+
+
+def test_kmeans_of_few_pivots():
+    g = _lattice(1000, 1000)
+    piv, dist = ssm.select_pivots(g, 3, with_dist=True)
+    _compare("k-means, k = 3", lambda: ssm.kmeans_pivots(piv, dist), {"km_chunk": 32}, 1.15)
