@@ -2341,7 +2341,7 @@ template <int W, bool M8, int SPOOL = kSelPool>
 __device__ __forceinline__ void select_ell_body(int n, const int* __restrict__ rp, const int* __restrict__ ci,
                                                 const int* __restrict__ ell, int k, int first, int* pivots, int* m,
                                                 int* gq, int* status, int wave_mode = 1, int t0 = 0,
-                                                int* pub = nullptr, int* ready = nullptr) {
+                                                int* pub = nullptr) {
     __shared__ __align__(16) unsigned char pool[SPOOL];
     __shared__ int2 s_slot[3];
     __shared__ int s_src;
@@ -2369,10 +2369,7 @@ __device__ __forceinline__ void select_ell_body(int n, const int* __restrict__ r
         __syncthreads();
         if (threadIdx.x == 0) {
             pivots[t] = src;
-            if (pub) {
-                __hip_atomic_store(pub + t, src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(ready, t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (pub) store_agent(pub + t, src);
             m[src] = 0;
             if (M8)
                 m8[src] = 0x80;  // m = 0, visited
@@ -2481,10 +2478,8 @@ __device__ __forceinline__ void select_ell_body(int n, const int* __restrict__ r
         if (threadIdx.x == 0) {
             if (t == 0 && (int)(best >> 32) == kInf) status[0] = 1;
             s_src = (int)(0xffffffffu - (unsigned)(best & 0xffffffffu));
-            if (pub && t == 0 && (int)(best >> 32) == kInf) {  // the unset ranks name node 0
-                for (int r = 1; r < k; ++r) __hip_atomic_store(pub + r, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(ready, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (pub && t == 0 && (int)(best >> 32) == kInf)  // the unset ranks name node 0
+                for (int r = 1; r < k; ++r) store_agent(pub + r, 0);
         }
         __syncthreads();
         if (t == 0 && (int)(best >> 32) == kInf) break;  // disconnected (uniform)
@@ -3538,11 +3533,11 @@ constexpr int kPoolSelBlock = 512;
 constexpr int kPoolBfsBlock = 256;
 
 // What the searches that follow the selections of a batch share with them:
-// per graph the ranks published (ready), the ranks taken (taken) and the first
-// of its entries in pub; per graph and rank the pivot (-1: not yet).
+// per graph the ranks taken and the first of its entries in pub; per graph and
+// rank the pivot (-1: not yet; written once, in ascending rank).
 struct PoolFollow {
-    int *ready, *taken, *first, *pub;
-    __device__ PoolFollow(int* p, int count) : ready(p), taken(p + count), first(p + 2 * count), pub(p + 3 * count) {}
+    int *taken, *first, *pub;
+    __device__ PoolFollow(int* p, int count) : taken(p), first(p + count), pub(p + 2 * count) {}
 };
 
 // Whether a batch's searches follow its selections: while every selection has
@@ -3555,8 +3550,7 @@ __global__ __launch_bounds__(kPoolSelBlock) void k_pool_select(const PoolGraph* 
     const PoolGraph& g = gs[blockIdx.x];
     const PoolFollow f(follow, gridDim.x);  // read with PUB alone
     select_ell_body<kPoolEllW, true, SPOOL>(g.n, g.rp, g.ci, g.ell, g.k, g.first, g.pivots, g.m, g.gq, g.info, 1, 0,
-                                            PUB ? f.pub + f.first[blockIdx.x] : nullptr,
-                                            PUB ? f.ready + blockIdx.x : nullptr);
+                                            PUB ? f.pub + f.first[blockIdx.x] : nullptr);
 }
 
 hipError_t pool_select(const PoolGraph* gs, int count, int nmax, int* follow, hipStream_t s) {
@@ -3586,7 +3580,7 @@ __global__ __launch_bounds__(kPoolBfsBlock) void k_pool_bfs(const PoolGraph* __r
 }
 
 // The BFS of the batch's pivots as they are published: a block takes the next
-// rank of any graph that has one ready, and runs it as k_pool_bfs does.  Run
+// rank of any graph whose pivot is there, and runs it as k_pool_bfs does.  Run
 // twice: beside the selections, where a block with nothing to take looks again
 // `looks` times in all and then ends (so the launch ends whatever becomes of
 // the selections), and after both, with looks = 0, for the ranks left.  A rank
@@ -3612,35 +3606,33 @@ __global__ __launch_bounds__(kPoolBfsBlock) void k_pool_bfs_follow(const PoolGra
         __syncthreads();
         for (int j = threadIdx.x; j < count; j += blockDim.x) {
             const int q = start + j < count ? start + j : start + j - count;
-            const int a = __hip_atomic_load(f.taken + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int r = __hip_atomic_load(f.ready + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (a < r) atomicMin(&s_pick, j);
-            if (a < gs[q].k) s_open = 1;
+            const int a = load_agent(f.taken + q), k = gs[q].k;
+            if (a < k) {
+                s_open = 1;
+                if (load_agent(f.pub + f.first[q] + a) >= 0) atomicMin(&s_pick, j);
+            }
         }
         __syncthreads();
         const int pick = s_pick, open = s_open;
         if (!open) return;  // the whole block
         if (pick == INT_MAX) {
             if (looks-- <= 0) return;  // the whole block
-            __builtin_amdgcn_s_sleep(32);
+            __builtin_amdgcn_s_sleep(127);  // about 3 us: looks are loads beside the selections
             continue;
         }
         const int q = start + pick < count ? start + pick : start + pick - count;
         if (threadIdx.x == 0) {
-            const int r = __hip_atomic_load(f.ready + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int a = __hip_atomic_load(f.taken + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            while (a < r && !__hip_atomic_compare_exchange_strong(f.taken + q, &a, a + 1, __ATOMIC_RELAXED,
-                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-            }
-            if (a < r) {
-                // its store was issued before that of `ready`, which has been
-                // seen: it arrives without anybody's doing
-                int v;
-                while ((v = __hip_atomic_load(f.pub + f.first[q] + a, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT)) < 0)
-                    __builtin_amdgcn_s_sleep(1);
-                s_rank = a;
-                s_src = v;
+            const int k = gs[q].k;
+            int a = load_agent(f.taken + q);
+            while (a < k) {  // ends: a failed swap means that another block took the rank
+                const int v = load_agent(f.pub + f.first[q] + a);
+                if (v < 0) break;
+                if (__hip_atomic_compare_exchange_strong(f.taken + q, &a, a + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT)) {
+                    s_rank = a;
+                    s_src = v;
+                    break;
+                }
             }
         }
         __syncthreads();

@@ -710,7 +710,7 @@ ssm_status wait_all(ssm_pool* p) {
     return SSM_OK;
 }
 
-constexpr int kFollowLooks = 4096;  // looks of an idle following block, 1 to 2 us each
+constexpr int kFollowLooks = 2048;  // looks of an idle following block, about 4 us each
 constexpr int kFollowPerCu = 2;     // following blocks per CU
 
 // The pool's second stream, made to wait for what s holds so far; s itself
@@ -1047,14 +1047,14 @@ ssm_status ssm_pool_prepare(ssm_pool* p, int32_t count, const int32_t* slots, in
         e = hipGetLastError();
     }
     // The BFS follow the selections on the second stream where that pays, from
-    // a record that takes the place of their items (3 + k ints per graph, k >=
+    // a record that takes the place of their items (2 + k ints per graph, k >=
     // 3, where the items are 2 k).
     hipStream_t aside = e == hipSuccess && pool_follows(nq) ? fork_side(p, s) : s;
     if (aside != s) {
         int* follow = (int*)dbi;
-        hf.assign(3 * (size_t)nq + nbfs, 0);
-        for (int q = 1; q < nq; ++q) hf[2 * nq + q] = hf[2 * nq + q - 1] + p->slots[ids[q - 1]].k;
-        std::fill(hf.begin() + 3 * nq, hf.end(), -1);
+        hf.assign(2 * (size_t)nq + nbfs, 0);
+        for (int q = 1; q < nq; ++q) hf[nq + q] = hf[nq + q - 1] + p->slots[ids[q - 1]].k;
+        std::fill(hf.begin() + 2 * nq, hf.end(), -1);
         e = hipMemcpyAsync(follow, hf.data(), sizeof(int) * hf.size(), hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = hipEventRecord(p->forked, s);
         if (e == hipSuccess) e = hipStreamWaitEvent(aside, p->forked, 0);

@@ -207,7 +207,7 @@ struct PoolGraph {
 // queue per block.
 hipError_t pool_prep_init(const PoolGraph* gs, int count, int nmax, hipStream_t s);
 // follow (optional): where the selections publish their pivots for
-// pool_bfs_follow, which runs the BFS beside them: per graph a 0, a 0 and the
+// pool_bfs_follow, which runs the BFS beside them: per graph a 0, per graph the
 // sum of k over the graphs before it, then per graph and rank a -1.
 bool pool_follows(int count);
 hipError_t pool_bfs_follow(const PoolGraph* gs, int count, int* follow, int looks, int* gq, long long gq_stride,
