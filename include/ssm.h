@@ -433,8 +433,8 @@ void ssm_release_cache(void);
  *   pool_graph -1 (ssm_pool_sweep launches each kernel instead of replaying
  *   a captured HIP graph of the quantum), pool_persist 1|-1 (the pooled
  *   sweep on a persistent grid, or a block per chunk, instead of the timed
- *   choice), pool_follow -1 (ssm_pool_prepare runs the BFS after the
- *   selections instead of beside them; same result).
+ *   choice), pool_follow -1|1 (ssm_pool_prepare runs the BFS after the
+ *   selections, or beside them up to one graph per compute unit; same result).
  * SSM_E_INVAL for an unknown name. */
 ssm_status ssm_set_variant(const char* name, int32_t value);
 

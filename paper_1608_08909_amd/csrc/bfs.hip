@@ -3540,10 +3540,20 @@ struct PoolFollow {
     __device__ PoolFollow(int* p, int count) : taken(p), first(p + count), pub(p + 2 * count) {}
 };
 
-// Whether a batch's searches follow its selections: while every selection has
-// a CU of its own, the rest of the device is idle beside them.  (tuning:
-// pool_follow -1 = never)
-bool pool_follows(int count) { return count <= num_cus() && variant("pool_follow") >= 0; }
+// Whether a batch's searches follow its selections: while the selections leave
+// CUs idle, and where the rows to run (`rows`: k n over the batch) weigh more
+// than the looks of the idle blocks, which slow the selections.  The whole
+// preparation in ms, after the selections -> beside them, by graphs x nodes (k):
+//   16 x 2,500 (50) 1.35 -> 1.98, 48 1.67 -> 1.72, 64 1.75 -> 1.69
+//   16 x 9,700 (100) 3.7 -> 4.5, 32 4.45 -> 4.35, 64 6.7 -> 5.9, 96 8.7 -> 7.9, 128
+//   10.5 -> 9.7, 192 14.2 -> 13.6, 224 16.0 -> 15.7, 256 18.1 -> 18.3
+//   8 x 30,000 (100) 7.5 -> 8.4, 16 9.2 -> 9.2, 24 11.3 -> 9.8, 64 17.5 -> 15.6
+// (tuning: pool_follow -1 = never, 1 = up to one graph per CU)
+bool pool_follows(int count, long long rows) {
+    const int v = variant("pool_follow");
+    if (v != 0) return v > 0 && count <= num_cus();
+    return 8 * count <= 7 * num_cus() && (double)count * (double)rows >= 6e8;
+}
 
 template <int SPOOL, bool PUB>
 __global__ __launch_bounds__(kPoolSelBlock) void k_pool_select(const PoolGraph* __restrict__ gs, int* follow) {

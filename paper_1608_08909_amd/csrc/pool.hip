@@ -999,13 +999,14 @@ ssm_status ssm_pool_prepare(ssm_pool* p, int32_t count, const int32_t* slots, in
     // per-call device buffers: descriptors, BFS items, Gram items, BFS
     // overflow queues, info copy
     int nmax = 0, kmax = 0, kpmax = 0;
-    long long nbfs = 0, ngram = 0;
+    long long nbfs = 0, ngram = 0, nrows = 0;
     for (int id : ids) {
         const Slot& sl = p->slots[id];
         nmax = std::max(nmax, sl.n);
         kmax = std::max(kmax, sl.k);
         kpmax = std::max(kpmax, tile_cols(sl.k) * 16);
         nbfs += sl.k;
+        nrows += (long long)sl.k * sl.n;
         const int T = tile_cols(sl.k);
         ngram += (long long)div_up(sl.n, kPoolGramChunk) * div_up(T * (T + 1) / 2, 32);
     }
@@ -1049,7 +1050,7 @@ ssm_status ssm_pool_prepare(ssm_pool* p, int32_t count, const int32_t* slots, in
     // The BFS follow the selections on the second stream where that pays, from
     // a record that takes the place of their items (2 + k ints per graph, k >=
     // 3, where the items are 2 k).
-    hipStream_t aside = e == hipSuccess && pool_follows(nq) ? fork_side(p, s) : s;
+    hipStream_t aside = e == hipSuccess && pool_follows(nq, nrows) ? fork_side(p, s) : s;
     if (aside != s) {
         int* follow = (int*)dbi;
         hf.assign(2 * (size_t)nq + nbfs, 0);

@@ -209,7 +209,7 @@ hipError_t pool_prep_init(const PoolGraph* gs, int count, int nmax, hipStream_t 
 // follow (optional): where the selections publish their pivots for
 // pool_bfs_follow, which runs the BFS beside them: per graph a 0, per graph the
 // sum of k over the graphs before it, then per graph and rank a -1.
-bool pool_follows(int count);
+bool pool_follows(int count, long long rows);
 hipError_t pool_bfs_follow(const PoolGraph* gs, int count, int* follow, int looks, int* gq, long long gq_stride,
                            int blocks, hipStream_t s);
 hipError_t pool_select(const PoolGraph* gs, int count, int nmax, int* follow, hipStream_t s);

@@ -93,3 +93,30 @@ def test_kmeans_of_few_pivots():
     g = _lattice(1000, 1000)
     piv, dist = ssm.select_pivots(g, 3, with_dist=True)
     _compare("k-means, k = 3", lambda: ssm.kmeans_pivots(piv, dist), {"km_chunk": 32}, 1.15)
+
+
+@pytest.mark.parametrize("count,n,k", [(16, 2500, 50), (64, 5000, 60)])
+def test_pool_preparation(count, n, k):
+    graphs = [G.rgg(n, q) for q in range(4)]
+    pool = ssm.Pool(1 << 32)
+
+    def best(reps=5):
+        times = []
+        for _ in range(reps):
+            slots = [pool.add(graphs[q % 4], k) for q in range(count)]
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            pool.prepare(slots)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t)
+            for q in slots:
+                pool.remove(q)
+        return min(times[1:])
+
+    own, alt = best(), []
+    for follow in (-1, 1):
+        with ssm.variants(pool_follow=follow):
+            alt.append(best())
+    print("case", count, n, k, [f"{1e3 * t:.3f} ms" for t in [own] + alt], flush=True)
+    assert own <= 1.1 * min(alt)
+    pool.close()
