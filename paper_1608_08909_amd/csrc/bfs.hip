@@ -2647,14 +2647,15 @@ constexpr long long kSelOneWgMaxN = 1LL << 18;
 // of its own, so the form pays from a number of pivots on, against one workgroup
 // (up to 2^18 nodes, about 140k of them with the byte copy of m; ms, one
 // workgroup -> ahead):
-//   meshes (mean degree 6)   41k: k = 16 2.07 -> 2.22, 32 2.79 -> 2.52; 132k: k = 32
-//                            6.36 -> 6.64, 48 7.28 -> 7.17; 250k: k = 12 7.37 -> 7.80,
-//                            24 9.96 -> 8.42
-//   geometric (degree 8)     41k: k = 16 2.15 -> 2.24, 32 2.81 -> 2.66; 132k: k = 16
-//                            6.46 -> 7.15, 32 8.00 -> 7.68; 160k: 24 8.75 -> 7.88
-//   lattices (degree 4)      41k: k = 64 3.99 -> 4.09, 100 4.83 -> 4.65; 132k: k = 32
-//                            6.77 -> 7.13, 64 8.68 -> 8.39; 250k: k = 24 10.4 -> 10.8,
-//                            32 12.2 -> 11.6
+//   meshes (mean degree 6)   50k: k = 32 3.15 -> 3.21, 48 3.65 -> 3.51; 100k: k = 24
+//                            4.43 -> 4.67, 40 5.30 -> 5.04; 132k: k = 32 6.36 -> 6.64,
+//                            48 7.28 -> 7.17; 250k: k = 12 7.37 -> 7.80, 24 9.96 -> 8.42
+//   geometric (degree 8)     41k: k = 16 2.15 -> 2.24, 32 2.81 -> 2.66; 85k: k = 12
+//                            3.77 -> 3.82, 20 4.50 -> 4.27; 132k: k = 24 7.31 -> 7.43, 32
+//                            8.00 -> 7.68; 160k: 24 8.75 -> 7.88
+//   lattices (degree 4)      41k: k = 64 3.99 -> 4.09, 100 4.83 -> 4.65; 90k: k = 64 6.65
+//                            -> 6.95, 100 8.02 -> 7.87; 132k: k = 32 6.77 -> 7.13, 64 8.68
+//                            -> 8.39; 250k: k = 24 10.4 -> 10.8, 32 12.2 -> 11.6
 // and against the grid above: mesh of 300k, k = 8 10.9 -> 8.2; 1.2M 25.4 -> 27.1,
 // k = 16 36.4 -> 31.8; 3.25M k = 8 45.0 -> 46.3, k = 16 63.5 -> 59.2.  Trees and
 // chains (mean degree about 2) are not foretold and hub graphs (a row above 64;
@@ -2670,7 +2671,13 @@ static int ahead_workers(const ssm_csr* g, int k) {
     int least = sel_bits_fit(n) ? 8 : 16;
     if (n <= kSelOneWgMaxN) {
         const bool lattice = 2LL * g->nnz < 9LL * n;  // a mean degree below 4.5
-        least = !sel_m8_fits(n) ? (lattice ? 32 : 24) : g->nnz >= 7LL * n ? 24 : lattice ? 96 : 48;
+        const bool many = g->nnz >= 7LL * n;
+        if (!sel_m8_fits(n))
+            least = lattice ? 32 : 24;
+        else if (n < 125000)
+            least = many ? 20 : lattice ? 96 : 40;
+        else  // little LDS is left for the queue
+            least = many ? 28 : lattice ? 64 : 48;
     }
     return k >= least ? kAheadWorkers : 0;
 }

@@ -56,8 +56,8 @@ def _layers(layers, width, seed):
     return G.csr_from_edges(layers * width, np.concatenate([np.stack([np.repeat(u, 3), v.ravel()], 1), last]), "layers")
 
 
-RULE = [(G.grid(205, 200), 95), (G.grid(205, 200), 96), (G.tri_grid(205, 200), 47), (G.tri_grid(205, 200), 48),
-        (G.rgg(42000, 3, 8.0), 23), (G.rgg(42000, 3, 8.0), 24), (G.tri_grid(199, 200), 60),
+RULE = [(G.grid(205, 200), 95), (G.grid(205, 200), 96), (G.tri_grid(205, 200), 39), (G.tri_grid(205, 200), 40),
+        (G.rgg(42000, 3, 8.0), 19), (G.rgg(42000, 3, 8.0), 20), (G.grid(360, 350), 64), (G.tri_grid(360, 350), 48), (G.tri_grid(199, 200), 60),
         (G.barabasi_albert(42000, 5, 2), 30), (G.tree_plus(42000, 5), 120), (_regular(42000, 1), 30),
         (_layers(100, 420, 2), 60), (G.grid(400, 390), 31), (G.grid(400, 390), 32),
         (G.tri_grid(400, 390), 23), (G.tri_grid(400, 390), 24), (G.tri_grid(520, 530), 7),
