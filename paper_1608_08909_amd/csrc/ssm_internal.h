@@ -43,7 +43,7 @@ struct ssm_terms {
     int32_t nseg = 0;              // segments of kHeavySeg arcs over the heavy rows
     int32_t* seg_start = nullptr;  // [nheavy + 1] first segment of each heavy row
     int32_t* seg_owner = nullptr;  // [nseg] heavy row of each segment
-    int2* seg_range = nullptr;     // [n] at a heavy node's id: its segments [x, y)
+    int2* seg_range = nullptr;     // [n] at a heavy node's id: its segments [x, y); elsewhere (-1, -1)
     float2* seg_sum = nullptr;     // [nseg] FP32 sweep scratch: neighbour displacement sum per segment
     double2* heavy_sum = nullptr;  // [nheavy] FP64 sweep scratch: numerator after a heavy row's neighbours
     // Node order of the FP32 sweep (all null when off): nodes sorted by

@@ -106,11 +106,13 @@ __global__ __launch_bounds__(256) void k_heavy_f64(int nheavy, const int* __rest
 }
 
 // A heavy node's neighbour sum (k_heavy_f64); seg_range and seg_owner name its
-// place in the heavy list.
+// place in the heavy list.  The list is that of the graph the terms were built
+// for: a long row of another one (same node and arc counts) is not in it.
 struct HubSums {
     const double2* sum;  // null: every row is summed by its own thread or lane group
     const int2* seg_range;
     const int* seg_owner;
+    __device__ __forceinline__ bool has(int i) const { return sum && seg_range[i].x >= 0; }
     __device__ __forceinline__ double2 of(int i) const { return sum[seg_owner[seg_range[i].x]]; }
 };
 
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(256) void k_sweep_f64(int n, int kpad, int W, const
         int zero = 0;
         const int e0 = rp[i];
         int e1 = rp[i + 1];
-        if (hubs.sum && e1 - e0 > kHeavyDegree) {
+        if (e1 - e0 > kHeavyDegree && hubs.has(i)) {
             const double2 v = hubs.of(i);
             nx = v.x;
             ny = v.y;
@@ -281,10 +283,26 @@ __global__ __launch_bounds__(256) void k_sweep_f64_terms(int n, int kpad, int W,
         __syncthreads();
         if (i < n && lane == 0) {
             double nx = 0.0, ny = 0.0;
-            if (hub) {
+            if (hub && hubs.has(i)) {
                 const double2 v = hubs.of(i);
                 nx = v.x;
                 ny = v.y;
+            } else if (hub) {  // as k_sweep_f64
+                int zero = 0;
+                for (int e = e0; e < rp[i + 1]; ++e) {
+                    const double2 xj = xo[ci[e]];
+                    const double dx = xi - xj.x, dy = yi - xj.y, r = sqrt(dx * dx + dy * dy);
+                    if (r > 0.0) {
+                        nx += xj.x + dx / r;
+                        ny += xj.y + dy / r;
+                    } else {
+                        ++zero;
+                    }
+                }
+                for (; zero > 0; --zero) {
+                    nx += xi;
+                    ny += yi;
+                }
             }
             for (int j = 0; j < deg; ++j) {
                 nx += T[j].x;
@@ -351,6 +369,7 @@ ssm_status heavy_segments(const ssm_csr* g, ssm_terms* t, hipStream_t s) {
     st = salloc((void**)&t->seg_start, sizeof(int) * ((size_t)nh + 1));
     if (st == SSM_OK) st = salloc((void**)&t->seg_range, sizeof(int2) * (size_t)g->n);
     if (st != SSM_OK) return st;
+    SSM_HIP(hipMemsetAsync(t->seg_range, 0xff, sizeof(int2) * (size_t)g->n, s));  // rows not in the list: -1
     const int hb = std::max(1, std::min(div_up(nh + 1, 256), 1024));
     // segment counts, then their exclusive scan (the last entry is the total)
     size_t scan_bytes = 0;
