@@ -51,7 +51,7 @@ def _lattice(rows, cols):
 def test_rows_of_a_mesh_too_large_for_the_pages():
     g = _lattice(1900, 1895)
     piv = torch.from_numpy(np.random.default_rng(7).choice(g.n, 40, replace=False).astype(np.int32)).cuda()
-    _compare("40 rows", lambda: ssm.bfs_pivots(g, piv), {"bfs_ring": -1}, 1.15)
+    _compare("40 rows", lambda: ssm.bfs_pivots(g, piv), {"bfs_ring": -1}, 1.3)
 
 
 def test_selections_of_several_threads():
@@ -73,7 +73,7 @@ def test_selections_of_several_threads():
         for t in threads:
             t.join()
 
-    _compare("4 threads", all_threads, {"select_ahead": -1}, 1.3)
+    _compare("4 threads", all_threads, {"select_ahead": -1}, 1.4)
     assert all(torch.equal(a, b) for a, b in zip(got, want))
 
 
@@ -81,18 +81,18 @@ def test_grid_selection_width():
     """The grid's levels with the rows padded as its lanes want them."""
     g = _lattice(1095, 1095)
     with ssm.variants(select_ahead=-1):
-        _compare("grid, k = 8", lambda: ssm.select_pivots(g, 8), {"ell_width": 16}, 1.06, reps=8)
+        _compare("grid, k = 8", lambda: ssm.select_pivots(g, 8), {"ell_width": 16}, 1.1, reps=8)
 
 
 def test_selection_of_few_pivots():
     g = _lattice(300, 300)
-    _compare("k = 8", lambda: ssm.select_pivots(g, 8), {"select_ahead": -1}, 1.12, reps=8)
+    _compare("k = 8", lambda: ssm.select_pivots(g, 8), {"select_ahead": -1}, 1.2, reps=8)
 
 
 def test_kmeans_of_few_pivots():
     g = _lattice(1000, 1000)
     piv, dist = ssm.select_pivots(g, 3, with_dist=True)
-    _compare("k-means, k = 3", lambda: ssm.kmeans_pivots(piv, dist), {"km_chunk": 32}, 1.15)
+    _compare("k-means, k = 3", lambda: ssm.kmeans_pivots(piv, dist), {"km_chunk": 32}, 1.3)
 
 
 @pytest.mark.parametrize("count,n,k", [(16, 2500, 50), (64, 5000, 60)])
@@ -118,5 +118,5 @@ def test_pool_preparation(count, n, k):
         with ssm.variants(pool_follow=follow):
             alt.append(best())
     print("case", count, n, k, [f"{1e3 * t:.3f} ms" for t in [own] + alt], flush=True)
-    assert own <= 1.1 * min(alt)
+    assert own <= 1.2 * min(alt)
     pool.close()

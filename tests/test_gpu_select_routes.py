@@ -22,11 +22,11 @@ def _check(g, k, first=0):
 @pytest.mark.parametrize("n,state", [(120000, 0), (200000, 0), (263000, 2), (263000, 3)],
                          ids=["bytes", "bits", "bits after the grid", "stamps"])
 def test_a_search_longer_than_the_barrier_waits(n, state, forced):
-    """Workgroups that wait for the search of a long path see it go on: 30,000
-    polls (about 20 ms) are far fewer than its levels take."""
+    """Workgroups that wait for the search of a long path see it go on: 60,000
+    polls (about 30 ms) are far fewer than its levels take."""
     forced("select_ahead", 4)
     forced("select_m8", state)
-    forced("bar_polls", 30000)
+    forced("bar_polls", 60000)
     _check(G.path(n), 4)
 
 
