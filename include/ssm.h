@@ -410,8 +410,8 @@ void ssm_release_cache(void);
  *   set, with or without a read before the swap), bfs_rowq 2,
  *   bfs_loads 2|3 (CSR rows: plain visited checks as well as plain CSR
  *   loads, or agent-scope loads throughout), bfs_grp -1 (CSR rows on one
- *   workgroup each instead of two), bfs_ring -1|1 (never, or
- *   always, the one-workgroup rows with paged visited bits), bfs_pages N
+ *   workgroup each instead of two), bfs_ring -1|1 (never, or up to 3,407,488
+ *   nodes always, the one-workgroup rows with paged visited bits), bfs_pages N
  *   (pages of visited bits at most, from 1024),
  *   bfs_lanes 2..64, msbfs -1|1 (never / always the bit-parallel BFS
  *   first; by default it goes first on graphs of at least 2^19 arcs whose

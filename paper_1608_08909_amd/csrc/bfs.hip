@@ -1134,10 +1134,11 @@ ssm_status mssp(const ssm_csr* g, int32_t k, const int32_t* pivots, int32_t* dis
         *dmax_out_host = host[k];
         return SSM_OK;
     }
-    // Too large for LDS visited bits: variant bfs_ell = 3 (or 4: without the
-    // read before the swap) takes the same padded-adjacency BFS with the
-    // distance row as visited set; the default is the CSR form below (faster
-    // on a 3.25M-node mesh: 57 against 84 ms for 100 rows without the read).
+    // Too large for LDS visited bits, and not mssp_ring's: variant bfs_ell = 3
+    // (or 4: without the read before the swap) takes the same padded-adjacency
+    // BFS with the distance row as visited set; the default is the CSR form below
+    // (on a 3.25M-node mesh with 16 slots per row and one workgroup per row in
+    // both, 57 against 84 ms for 100 rows without the read).
     if (variant("bfs_ell") == 3 || variant("bfs_ell") == 4) {
         const int W = ell_width(g, s);
         const long long qcap = 1LL << 31;  // overflow ints (8 GiB)
@@ -2555,8 +2556,8 @@ __global__ __launch_bounds__(256) void k_row_shape(int n, const int* __restrict_
 }
 
 // Whether the rows go to k_bfs_ring.  Against k_bfs_grp's two workgroups per
-// row: 100 rows of a 3.25M-node mesh 30.3 against 37.3 ms, 16 rows 28.8 against
-// 29.5, 8 rows 29.6 against 27.9 (two workgroups have the memory to themselves):
+// row: 100 rows of a 3.25M-node mesh 29.8 against 37.4 ms, 16 rows 28.3 against
+// 30.0, 8 rows 29.6 against 27.9 (two workgroups have the memory to themselves):
 // from 16 rows on.  Rows of at most 8 entries (37.7 ms with padded rows of 16),
 // three on average (trees' levels are wide: 100 rows of a binary tree of 1.5M
 // nodes 11.5 against 11.0 ms), and a numbering that keeps neighbours of
@@ -3603,9 +3604,9 @@ __global__ __launch_bounds__(kPoolBfsBlock) void k_pool_bfs(const PoolGraph* __r
 // the selections), and after both, with looks = 0, for the ranks left.  A rank
 // taken is always done by its taker, so those left are taken[q] .. k - 1.
 // Blocks begin to look at different graphs.  96 graphs of about 9700 nodes, k =
-// 95 to 100: selections 4.7 ms, then 9600 BFS 3.8 ms; so, the whole call took
-// 30.9 ms instead of 33.6 (with 2 following blocks per CU; 33.3 with 1, 31.5
-// with 3, 32.4 with 4, which slow the selections).
+// 95 to 100, alone: selections 4.7 ms, then 9600 BFS 3.8 ms; beside each other
+// the preparation takes 7.9 ms instead of 8.7 (with 2 following blocks per CU: of
+// a whole call's 30.9 ms, 1, 3 and 4 per CU made 33.3, 31.5 and 32.4).
 __global__ __launch_bounds__(kPoolBfsBlock) void k_pool_bfs_follow(const PoolGraph* __restrict__ gs, int count,
                                                                    int* follow, int looks, int* gq,
                                                                    long long gq_stride) {

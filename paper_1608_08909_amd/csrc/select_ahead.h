@@ -20,15 +20,15 @@
 // distance to the candidates taken so far).  The bound is the largest
 // |d(l, u) - d(l, v)| over the landmarks l = pivots 0, 1, 2, whose full rows
 // more workgroups compute beside the first rounds.  On a 100k-node geometric
-// graph, k = 200, 38 rounds remain, on a 150k-node mesh, k = 150, 25.  Trees
-// are not foretold, and the guessing stops when it does not pay.
+// graph, k = 200, 38 rounds remain, on a 150k-node mesh, k = 150, 25.  The
+// guessing stops when it does not pay.
 //
 // Bound by the chain of levels of the first, hardly foretold pivots (35 of
 // the 52 ms of searches on the 3.25M-node mesh).  Measured, against the
-// searches one by one: 100k-node geometric graph, k = 200, 12.3 -> 9.0 ms;
-// mesh of 150k nodes, k = 150, 17.4 -> 10.1 ms; 500k, k = 100, 49.6 -> 23.8;
-// 900k 65 -> 38; 3.25M 133-147 -> 80 ms.  8 workers: 4 and 16 took 5 to 20 %
-// longer on the smaller graphs.
+// searches one by one: 100k-node geometric graph, k = 200, 12.5 -> 8.4 ms;
+// mesh of 150k nodes, k = 150, 18.2 -> 9.2 ms; 700k, k = 64, 46.7 -> 22.8; 3.25M,
+// k = 100, 133 -> 78 ms.  8 workers: 4 and 16 took 5 to 20 % longer on the
+// smaller graphs.  For which graphs and k: ahead_workers.
 #pragma once
 
 namespace ssm {
